@@ -27,6 +27,7 @@
 #include <cmath>
 
 #include "kernels.h"
+#include "wave_ops.h"
 
 namespace duet {
 namespace {
@@ -41,30 +42,6 @@ constexpr float kRescaleSlack = 8.0f;  // base-2 units: probabilities stay below
 constexpr int kRing = 4;  // page buffers per wave: kRing - 1 pages in flight
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-
-__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
-
-// Combine a value across the four 16-lane rows of a wave (lanes l, l ^ 16, l ^ 32, l ^ 48) with
-// the row-swap permutes, which stay in the vector ALU: an LDS permute would be counted with the
-// scalar loads, so waiting for it would also wait for them.
-__device__ __forceinline__ float max_rows(float x) {
-  const unsigned u = __float_as_uint(x);
-  auto s32 = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  const float m = fmaxf(__uint_as_float(s32[0]), __uint_as_float(s32[1]));
-  const unsigned v = __float_as_uint(m);
-  auto s16 = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-  return fmaxf(__uint_as_float(s16[0]), __uint_as_float(s16[1]));
-}
-__device__ __forceinline__ float sum_rows(float x) {
-  const unsigned u = __float_as_uint(x);
-  auto s16 = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const float m = __uint_as_float(s16[0]) + __uint_as_float(s16[1]);  // rows (0+1, 0+1, 2+3, 2+3)
-  const unsigned v = __float_as_uint(m);
-  auto s32 = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return __uint_as_float(s32[0]) + __uint_as_float(s32[1]);
-}
 
 // K/V pages are read exactly once per iteration (plain loads: non-temporal loads were measured
 // slower under the split).
@@ -94,8 +71,6 @@ __device__ __forceinline__ void load_page(Page<D>& pg, const char* kbase, const 
 #pragma unroll
   for (int n = 0; n < D / 16; ++n) pg.v[n] = stream_load<uint2>(vp + n * 16 * 32);
 }
-
-__device__ __forceinline__ bool page_ok(int id, long long num_phys) { return id >= 0 && (long long)id < num_phys; }
 
 // Uniform loads of the read-only work list through the scalar cache (used before the page stream
 // starts; inside it a scalar load would be waited for together with every LDS operation).
@@ -467,70 +442,6 @@ __global__ __launch_bounds__(256, 1) void decode_partial_bf16(AttnArgs a, WorkAr
   merge_tail();
 }
 
-// fp32 path (small shapes): one wave per item, lane = dim, scores reduced across the wave.
-template <int D>
-__global__ __launch_bounds__(256) void decode_partial_f32(AttnArgs a, WorkArgs w) {
-  constexpr int E = D / 64;
-  const int wave = uniform(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  const int4 dr = w.dreq[blockIdx.y];
-  const int witem = blockIdx.x * 4 + wave;
-  const int j = witem / dr.z;
-  const int s = witem - j * dr.z;
-  if (j >= a.h_kv) return;
-  const int4 m = w.meta[dr.x];
-  const int L = m.w + m.z;
-  const int g = a.group;
-  const int pb = s * w.pages_per_split;
-  const int pe = min(pb + w.pages_per_split, dr.w);
-  const float* K = reinterpret_cast<const float*>(a.k_cache);
-  const float* V = reinterpret_cast<const float*>(a.v_cache);
-  const int* prow = a.page_table + (size_t)dr.x * a.max_pages;
-  const int item = dr.y + j * dr.z + s;
-  int bad = 0;
-  for (int col = 0; col < g; ++col) {
-    const float* qrow = reinterpret_cast<const float*>(a.q) + ((size_t)m.y * a.h_q + j * g + col) * D;
-    float qv[E], acc[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      qv[e] = qrow[lane + 64 * e];
-      acc[e] = 0.f;
-    }
-    float m_run = -INFINITY, l_run = 0.f;
-    for (int p = pb; p < pe; ++p) {
-      const int id = uniform(prow[p]);
-      if (!page_ok(id, a.num_phys_pages)) {
-        bad = 1;
-        continue;
-      }
-      const size_t slab = ((size_t)id * a.h_kv + j) * 16 * D;
-      for (int t = 0; t < 16 && 16 * p + t < L; ++t) {
-        float dot = 0.f;
-#pragma unroll
-        for (int e = 0; e < E; ++e) dot += qv[e] * K[slab + (size_t)t * D + lane + 64 * e];
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) dot += __shfl_xor(dot, off);
-        const float x = dot * a.scale_log2;
-        const float m_new = fmaxf(m_run, x);
-        const float alpha = fast_exp2(m_run - m_new);
-        const float pr = fast_exp2(x - m_new);
-        l_run = l_run * alpha + pr;
-#pragma unroll
-        for (int e = 0; e < E; ++e) acc[e] = acc[e] * alpha + pr * V[slab + (size_t)(lane + 64 * e) * 16 + t];
-        m_run = m_new;
-      }
-    }
-    float* pa = w.pacc + ((size_t)item * g + col) * D;
-#pragma unroll
-    for (int e = 0; e < E; ++e) pa[lane + 64 * e] = acc[e];
-    if (lane == 0) {
-      w.pml[((size_t)item * g + col) * 2 + 0] = m_run;
-      w.pml[((size_t)item * g + col) * 2 + 1] = l_run;
-    }
-  }
-  if (bad && lane == 0) atomicOr(w.err, 1);
-}
-
 // Merges every (decode request, query head) pair of one layer: one wave per pair.
 template <int D, typename OutT>
 __global__ __launch_bounds__(256) void decode_reduce(AttnArgs a, WorkArgs w) {
@@ -570,15 +481,9 @@ hipError_t launch_persistent(const AttnArgs& a, const WorkArgs& w, hipStream_t s
 
 hipError_t launch_decode_partial(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
   if (w.n_dreq == 0) return hipSuccess;
-  const dim3 grid((a.h_kv * w.max_split + 3) / 4, w.n_dreq);
-  if (a.dtype == 0) {
-    if (w.pages_per_split != kDecodePagesPerSplit) return hipErrorInvalidValue;
-    return a.head_dim == 128 ? launch_persistent<128>(a, w, s) : launch_persistent<64>(a, w, s);
-  } else {
-    if (a.head_dim == 128) hipLaunchKernelGGL(decode_partial_f32<128>, grid, dim3(256), 0, s, a, w);
-    else hipLaunchKernelGGL(decode_partial_f32<64>, grid, dim3(256), 0, s, a, w);
-  }
-  return hipGetLastError();
+  if (a.dtype != 0) return launch_decode_partial_f32(a, w, s);
+  if (w.pages_per_split != kDecodePagesPerSplit) return hipErrorInvalidValue;
+  return a.head_dim == 128 ? launch_persistent<128>(a, w, s) : launch_persistent<64>(a, w, s);
 }
 
 hipError_t launch_decode_reduce(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {

@@ -34,6 +34,7 @@
 #include <cmath>
 
 #include "kernels.h"
+#include "wave_ops.h"
 
 namespace duet {
 namespace {
@@ -49,14 +50,11 @@ constexpr int kStages = 4;
 static_assert(kStages >= 2, "the ring needs a tile in use and one in flight");
 constexpr float kRescaleSlack = 8.0f;  // base-2 units: probabilities stay below 2^8
 
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 // Direct global-to-LDS load of 16 bytes per lane: lane i of the wave writes lds_block + 16 i.
 // lds_block must be the same for the whole wave.
 __device__ __forceinline__ void load_lds16(const char* src, __bf16* lds_block) {
   __builtin_amdgcn_global_load_lds(src, lds_block, 16, 0, 0);
 }
-__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ __forceinline__ bool page_ok(int id, long long num_phys) { return id >= 0 && (long long)id < num_phys; }
 
 // Max and sum of a value over lanes l and l ^ 32, by the half-wave swap permute (a vector-ALU op;
 // an LDS permute would wait behind the fragment reads in flight).  The swap returns the lane's own
@@ -485,61 +483,6 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_bf16(AttnArgs a, WorkArgs
   }
 }
 
-// fp32 path (small shapes): each wave walks its 32 rows one by one, lane = dim.
-template <int D>
-__global__ __launch_bounds__(256) void prefill_f32(AttnArgs a, WorkArgs w) {
-  constexpr int E = D / 64;
-  const int wave = uniform(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  const int4 it = w.pitems[blockIdx.x];  // (req, query head, q_row0, 0)
-  const int r = it.x, h = it.y, q_row0 = it.z;
-  const int4 m = w.meta[r];
-  const int q_start = m.y, q_len = m.z, c = m.w;
-  const int j = h / a.group;
-  const float* K = reinterpret_cast<const float*>(a.k_cache);
-  const float* V = reinterpret_cast<const float*>(a.v_cache);
-  const int* prow = a.page_table + (size_t)r * a.max_pages;
-  int bad = 0;
-  for (int i = 0; i < 32; ++i) {
-    const int qi = q_row0 + 32 * wave + i;
-    if (qi >= q_len) break;
-    const float* qrow = reinterpret_cast<const float*>(a.q) + ((size_t)(q_start + qi) * a.h_q + h) * D;
-    float qv[E], acc[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      qv[e] = qrow[lane + 64 * e];
-      acc[e] = 0.f;
-    }
-    float m_run = -INFINITY, l_run = 0.f;
-    const int pos = c + qi;
-    for (int t = 0; t <= pos; ++t) {
-      const int id = uniform(prow[t >> 4]);
-      if (!page_ok(id, a.num_phys_pages)) {
-        bad = 1;
-        continue;
-      }
-      const size_t slab = ((size_t)id * a.h_kv + j) * 16 * D;
-      float dot = 0.f;
-#pragma unroll
-      for (int e = 0; e < E; ++e) dot += qv[e] * K[slab + (size_t)(t & 15) * D + lane + 64 * e];
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) dot += __shfl_xor(dot, off);
-      const float x = dot * a.scale_log2;
-      const float m_new = fmaxf(m_run, x);
-      const float alpha = fast_exp2(m_run - m_new);
-      const float pr = fast_exp2(x - m_new);
-      l_run = l_run * alpha + pr;
-#pragma unroll
-      for (int e = 0; e < E; ++e) acc[e] = acc[e] * alpha + pr * V[slab + (size_t)(lane + 64 * e) * 16 + (t & 15)];
-      m_run = m_new;
-    }
-    float* orow = reinterpret_cast<float*>(a.out) + ((size_t)(q_start + qi) * a.h_q + h) * D;
-#pragma unroll
-    for (int e = 0; e < E; ++e) orow[lane + 64 * e] = acc[e] / l_run;
-  }
-  if (bad && lane == 0) atomicOr(w.err, 1);
-}
-
 template <int D, int NH>
 hipError_t launch_bf16(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
   static bool attr_set = false;  // the attribute is per function and process
@@ -587,10 +530,7 @@ size_t prefill_slot_bytes(int head_dim) { return (size_t)kThreads * (head_dim / 
 hipError_t launch_prefill(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
   if (w.n_pitems == 0) return hipSuccess;
   if (a.dtype == 0) return a.head_dim == 128 ? launch_bf16_nh<128>(a, w, s) : launch_bf16_nh<64>(a, w, s);
-  const dim3 grid(w.n_pitems);
-  if (a.head_dim == 128) hipLaunchKernelGGL(prefill_f32<128>, grid, dim3(256), 0, s, a, w);
-  else hipLaunchKernelGGL(prefill_f32<64>, grid, dim3(256), 0, s, a, w);
-  return hipGetLastError();
+  return launch_prefill_f32(a, w, s);
 }
 
 }  // namespace duet

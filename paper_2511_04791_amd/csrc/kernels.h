@@ -84,7 +84,7 @@ constexpr int kDecodeCounterInts = 2 * kDecodeSetInts;
 // Keys a prefill request may attend (its page ids are staged in LDS: 8192 ids, 32 KB).
 constexpr int kMaxPrefillKeys = 131072;
 
-constexpr int kPrefillRows = 128;  // query rows per fp32 prefill item (4 waves x 32)
+constexpr int kPrefillRows = 128;  // query rows per fp32 prefill item (8 workgroups x 16)
 constexpr int kPrefillKeys = 64;   // keys per LDS stage (4 pages)
 
 // bf16 prefill work unit: prefill_heads_per_unit(group) query heads of one GQA group times
@@ -139,6 +139,9 @@ hipError_t launch_qkv_split(const QkvSplitArgs& a, int rows, hipStream_t s);
 hipError_t launch_decode_partial(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
 hipError_t launch_decode_reduce(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
 hipError_t launch_prefill(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
+// The fp32 paths of the two launchers above.
+hipError_t launch_decode_partial_f32(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
+hipError_t launch_prefill_f32(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
 // Writes the new token of every decode request in w.dreq (position = meta cached_len).
 hipError_t launch_kv_append(const AppendArgs& a, const WorkArgs& w, hipStream_t s);
 

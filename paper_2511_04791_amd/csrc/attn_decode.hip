@@ -3,9 +3,10 @@
 // Each decode request has one query token at absolute position kv_len - 1 that attends all
 // kv_len keys (paper, Section 2: the new token's key and value are appended before attention;
 // Section 4.1: decode is q = 1, c > 0).  The work is HBM-bound: every key and value is read
-// once.  A work item is (request, kv head, split) where a split is a fixed run of logical pages
-// (pages_per_split).  One wave owns one item and reads each page of its kv head once for all
-// query heads of the GQA group, so the bytes moved are the algorithmic K/V bytes.
+// once.  A work item is (request, kv head, split) where a split is a run of logical pages of a
+// length that the batch fixes (kernels.h, decode_rule).  One wave owns one item and reads each page
+// of its kv head once for all query heads of the GQA group, so the bytes moved are the algorithmic
+// K/V bytes.
 //
 // bf16 path, per page (16 tokens), on MFMA with fp32 accumulate:
 //   S^T [16 tokens x 16 heads] = K_page [16 x d] . Q^T [d x 16]   (16x16x32, one per 32 dims)
@@ -19,6 +20,9 @@
 // reference max, denominator) go to the workspace, and one wave per (request, query head) merges
 // the splits: the reduce kernel, or, for the layers of a call but the last, the next layer's bf16
 // partial kernel, in the waves whose item queue has run dry.
+//
+// A batch of few items (kernels.h, decode_rule) cannot fill the chip with one wave per item: it runs
+// one workgroup per item instead (decode_small_bf16).
 // All arithmetic order depends on logical token positions only.
 #include <hip/hip_runtime.h>
 
@@ -61,15 +65,23 @@ struct Page {
 };
 
 template <int D>
-__device__ __forceinline__ void load_page(Page<D>& pg, const char* kbase, const char* vbase, size_t slab, int lane) {
-  const int row = lane & 15, quad = lane >> 4;
+__device__ __forceinline__ void load_k(Page<D>& pg, const char* kbase, size_t slab, int lane) {
   constexpr size_t kPageBytes = 16 * D * 2;  // one (page, kv head) slab
-  const char* kp = kbase + slab * kPageBytes + row * D * 2 + quad * 16;
-  const char* vp = vbase + slab * kPageBytes + row * 32 + quad * 8;
+  const char* kp = kbase + slab * kPageBytes + (lane & 15) * D * 2 + (lane >> 4) * 16;
 #pragma unroll
   for (int ks = 0; ks < D / 32; ++ks) pg.k[ks] = stream_load<uint4>(kp + ks * 64);
+}
+template <int D>
+__device__ __forceinline__ void load_v(Page<D>& pg, const char* vbase, size_t slab, int lane) {
+  constexpr size_t kPageBytes = 16 * D * 2;
+  const char* vp = vbase + slab * kPageBytes + (lane & 15) * 32 + (lane >> 4) * 8;
 #pragma unroll
   for (int n = 0; n < D / 16; ++n) pg.v[n] = stream_load<uint2>(vp + n * 16 * 32);
+}
+template <int D>
+__device__ __forceinline__ void load_page(Page<D>& pg, const char* kbase, const char* vbase, size_t slab, int lane) {
+  load_k<D>(pg, kbase, slab, lane);
+  load_v<D>(pg, vbase, slab, lane);
 }
 
 // Uniform loads of the read-only work list through the scalar cache (used before the page stream
@@ -442,6 +454,163 @@ __global__ __launch_bounds__(256, 1) void decode_partial_bf16(AttnArgs a, WorkAr
   merge_tail();
 }
 
+// Few items: one workgroup of 8 waves per item, each wave up to kSmallPages pages, all of their keys
+// in flight at once.  A lone wave streams an item's 256 KiB in about 25 us whatever the rest of the
+// chip does, since only three pages of it are in flight; eight waves with four pages each have
+// the whole item in flight, and the time is one descriptor, one page-id and one page latency, then
+// a merge of the waves through LDS.  Four requests of 620 .. 2783 tokens
+// (32 / 8 heads of 128): 26.7 us before, 10.8 us now.
+constexpr int kSmallWaves = 8;
+constexpr int kSmallThreads = 64 * kSmallWaves;
+constexpr int kSmallPages = kDecodePagesPerSplit / kSmallWaves;
+static_assert(kSmallPages * kSmallWaves == kDecodePagesPerSplit, "the waves cover a split");
+static_assert(kSmallPages % 2 == 0, "values are consumed two pages at a time");
+
+template <int D>
+__global__ __launch_bounds__(kSmallThreads, 4) void decode_small_bf16(AttnArgs a, WorkArgs w) {
+  constexpr int P = kSmallPages;
+  constexpr int kStride = D + 4;  // floats per head in LDS: heads start on different banks
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  const int tid = threadIdx.x;
+  const int wave = uniform(tid >> 6);
+  const int lane = tid & 63;
+  const int col = lane & 15, quad = lane >> 4;
+  const int g = a.group;
+  const DItem it = unpack_item(sload4(w.ditems + blockIdx.x), true);
+  const int n_pages = (it.n_tok + 15) >> 4;
+
+  // Pages wave, wave + 8, ... of the item.
+  const int* prow = a.page_table + (size_t)it.req * a.max_pages + it.first_page;
+  const int mine = lane < P && wave + kSmallWaves * lane < n_pages ? prow[wave + kSmallWaves * lane] : 0;
+  bf16x8 qf[D / 32];
+  const __bf16* qrow = reinterpret_cast<const __bf16*>(a.q) + ((size_t)it.q_start * a.h_q + it.j * g + col) * D + quad * 8;
+#pragma unroll
+  for (int ks = 0; ks < D / 32; ++ks) {
+    const uint4 u = col < g ? *reinterpret_cast<const uint4*>(qrow + ks * 32) : make_uint4(0, 0, 0, 0);
+    qf[ks] = __builtin_bit_cast(bf16x8, u);
+  }
+  // Every key page and the first half of the value pages load at once; the other half follows the
+  // scores, so the wave fits in 128 registers and four workgroups in a CU.
+  Page<D> pg[P];
+  bool ok[P], bad = false;
+  size_t slab[P];
+  auto values = [&](int u) {
+    if (ok[u]) {
+      load_v<D>(pg[u], reinterpret_cast<const char*>(a.v_cache), slab[u], lane);
+    } else {
+#pragma unroll
+      for (int n = 0; n < D / 16; ++n) pg[u].v[n] = make_uint2(0, 0);
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < P; ++u) {
+    const int id = __builtin_amdgcn_readlane(mine, u);
+    const bool there = wave + kSmallWaves * u < n_pages;
+    ok[u] = there && page_ok(id, a.num_phys_pages);
+    bad |= there && !ok[u];
+    slab[u] = (size_t)(ok[u] ? id : 0) * a.h_kv + it.j;
+    if (ok[u]) {
+      load_k<D>(pg[u], reinterpret_cast<const char*>(a.k_cache), slab[u], lane);
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < D / 32; ++ks) pg[u].k[ks] = make_uint4(0, 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < P / 2; ++u) values(u);
+  f32x4 sc[P];
+#pragma unroll
+  for (int u = 0; u < P; ++u) {
+    sc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < D / 32; ++ks)
+      sc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pg[u].k[ks]), qf[ks], sc[u], 0, 0, 0);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = P / 2; u < P; ++u) values(u);
+  float mx = -INFINITY;
+#pragma unroll
+  for (int u = 0; u < P; ++u)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (!ok[u] || 16 * (wave + kSmallWaves * u) + 4 * quad + i >= it.n_tok) sc[u][i] = -INFINITY;
+      mx = fmaxf(mx, sc[u][i]);
+    }
+  const float m = max_rows(mx) * a.scale_log2;
+  const float m_sub = m == -INFINITY ? 0.f : m;  // a wave without tokens: every weight is 2^-inf = 0
+  bf16x4 pb[P];
+  float l = 0.f;
+  const bf16x2 ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
+#pragma unroll
+  for (int u = 0; u < P; ++u) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) pb[u][i] = static_cast<__bf16>(fast_exp2(__builtin_fmaf(sc[u][i], a.scale_log2, -m_sub)));
+    // The denominator sums the bf16 probabilities the PV product consumes.
+    l = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pb[u][0], pb[u][1]}, ones, l, false);
+    l = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pb[u][2], pb[u][3]}, ones, l, false);
+  }
+  l = sum_rows(l);
+  // Values two pages at a time: the contraction slots 0 .. 3 of a lane are the first page's
+  // tokens 4 quad .. + 3, slots 4 .. 7 the second page's, in both operands.
+  f32x4 acc[D / 16];
+#pragma unroll
+  for (int n = 0; n < D / 16; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int u = 0; u < P; u += 2) {
+    uint64_t mk[2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)  // values past the end must not reach the MFMA (0 x NaN is NaN)
+      mk[x] = low_elems_mask(it.n_tok - (16 * (wave + kSmallWaves * (u + x)) + 4 * quad));
+    const bf16x8 pf = {pb[u][0], pb[u][1], pb[u][2], pb[u][3], pb[u + 1][0], pb[u + 1][1], pb[u + 1][2], pb[u + 1][3]};
+#pragma unroll
+    for (int n = 0; n < D / 16; ++n) {
+      const uint64_t v0 = ((uint64_t)pg[u].v[n].y << 32 | pg[u].v[n].x) & mk[0];
+      const uint64_t v1 = ((uint64_t)pg[u + 1].v[n].y << 32 | pg[u + 1].v[n].x) & mk[1];
+      const uint4 vf = make_uint4((unsigned)v0, (unsigned)(v0 >> 32), (unsigned)v1, (unsigned)(v1 >> 32));
+      acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf), pf, acc[n], 0, 0, 0);
+    }
+  }
+  if (bad && lane == 0) atomicOr(w.err, 1);
+
+  float* const ml = lds + kSmallWaves * g * kStride;  // [wave][g][2]
+  if (col < g) {
+    float* st = lds + (wave * g + col) * kStride;
+#pragma unroll
+    for (int n = 0; n < D / 16; ++n) *reinterpret_cast<f32x4*>(st + 16 * n + 4 * quad) = acc[n];
+    if (quad == 0) *reinterpret_cast<float2*>(ml + (wave * g + col) * 2) = make_float2(m, l);
+  }
+  __syncthreads();
+  // The waves in order, against their common max, one thread per four dims: the item's partial,
+  // or the output itself where no request has a second split (there is no reduce kernel then).
+  for (int x = tid; x < g * D / 4; x += kSmallThreads) {
+    const int c = x / (D / 4), e = 4 * (x % (D / 4));
+    float mm = -INFINITY;
+#pragma unroll
+    for (int v = 0; v < kSmallWaves; ++v) mm = fmaxf(mm, ml[(v * g + c) * 2]);
+    const float mm_sub = mm == -INFINITY ? 0.f : mm;
+    float den = 0.f;
+    f32x4 num = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int v = 0; v < kSmallWaves; ++v) {
+      const float2 t = *reinterpret_cast<const float2*>(ml + (v * g + c) * 2);
+      const float wgt = fast_exp2(t.x - mm_sub);
+      den += wgt * t.y;
+      num += wgt * *reinterpret_cast<const f32x4*>(lds + (v * g + c) * kStride + e);
+    }
+    if (w.max_split == 1) {
+      const float inv = 1.0f / den;
+      bf16x4 o;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[i] = static_cast<__bf16>(num[i] * inv);
+      *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(a.out) + ((size_t)it.q_start * a.h_q + it.j * g) * D + 4 * x) = o;
+    } else {
+      *reinterpret_cast<f32x4*>(w.pacc + (size_t)it.slot * g * D + 4 * x) = num;
+      if (e == 0) *reinterpret_cast<float2*>(w.pml + ((size_t)it.slot * g + c) * 2) = make_float2(mm, den);
+    }
+  }
+}
+
 // Merges every (decode request, query head) pair of one layer: one wave per pair.
 template <int D, typename OutT>
 __global__ __launch_bounds__(256) void decode_reduce(AttnArgs a, WorkArgs w) {
@@ -462,12 +631,12 @@ constexpr int kMinWavesPerCu = 4;  // waves per CU of the share, at least
 // is sized for at least kMinRounds items per wave (a short tail when the last items
 // finish), but never below kMinWavesPerCu waves per CU (bandwidth on small CU
 // shares) nor above what is resident at once.
-template <int D>
+template <int D, int PPS>
 hipError_t launch_persistent(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
   static int per_cu = 0;  // resident 256-thread blocks per CU, from the occupancy calculator
   if (per_cu == 0) {
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &per_cu, reinterpret_cast<const void*>(&decode_partial_bf16<D, kDecodePagesPerSplit>), 256, 0);
+        &per_cu, reinterpret_cast<const void*>(&decode_partial_bf16<D, PPS>), 256, 0);
     if (e != hipSuccess) return e;
     if (per_cu < 1) per_cu = 1;
   }
@@ -475,19 +644,38 @@ hipError_t launch_persistent(const AttnArgs& a, const WorkArgs& w, hipStream_t s
   const int floor_waves = w.decode_cus * kMinWavesPerCu;
   const int want = (w.n_ditems + kMinRounds - 1) / kMinRounds;
   const int waves = std::max(1, std::min(capacity, std::max(want, floor_waves)));
-  hipLaunchKernelGGL((decode_partial_bf16<D, kDecodePagesPerSplit>), dim3((waves + 3) / 4), dim3(256), 0, s, a, w);
+  hipLaunchKernelGGL((decode_partial_bf16<D, PPS>), dim3((waves + 3) / 4), dim3(256), 0, s, a, w);
+  return hipGetLastError();
+}
+
+template <int D>
+hipError_t launch_small(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
+  // Per wave the item's [g][D + 4] output and [g][2] (m, l): at most 68.6 KB (16 heads of 128).
+  const auto lds_bytes = [](int g) { return (size_t)kSmallWaves * g * (D + 4 + 2) * sizeof(float); };
+  static bool attr_set = false;  // the attribute is per function and process
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_small_bf16<D>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(16));
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  hipLaunchKernelGGL(decode_small_bf16<D>, dim3(w.n_ditems), dim3(kSmallThreads), lds_bytes(a.group), s, a, w);
   return hipGetLastError();
 }
 
 hipError_t launch_decode_partial(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
   if (w.n_dreq == 0) return hipSuccess;
   if (a.dtype != 0) return launch_decode_partial_f32(a, w, s);
-  if (w.pages_per_split != kDecodePagesPerSplit) return hipErrorInvalidValue;
-  return a.head_dim == 128 ? launch_persistent<128>(a, w, s) : launch_persistent<64>(a, w, s);
+  if (w.decode_small) return a.head_dim == 128 ? launch_small<128>(a, w, s) : launch_small<64>(a, w, s);
+  if (w.decode_pps == kDecodePagesPerSplitShort)
+    return a.head_dim == 128 ? launch_persistent<128, kDecodePagesPerSplitShort>(a, w, s)
+                             : launch_persistent<64, kDecodePagesPerSplitShort>(a, w, s);
+  return a.head_dim == 128 ? launch_persistent<128, kDecodePagesPerSplit>(a, w, s)
+                           : launch_persistent<64, kDecodePagesPerSplit>(a, w, s);
 }
 
 hipError_t launch_decode_reduce(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
-  if (w.n_dreq == 0) return hipSuccess;
+  if (w.n_dreq == 0 || (w.decode_small && w.max_split == 1)) return hipSuccess;  // nothing to merge
   const dim3 grid((w.n_dreq * a.h_q + 3) / 4);
   if (a.dtype == 0) {
     if (a.head_dim == 128) hipLaunchKernelGGL((decode_reduce<128, __bf16>), grid, dim3(256), 0, s, a, w);

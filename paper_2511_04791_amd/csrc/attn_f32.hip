@@ -219,7 +219,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void prefill_f32(AttnArgs a, WorkAr
   }
 }
 
-// One wave per (request, kv head, split of pages_per_split pages).
+// One wave per (request, kv head, split of kDecodePagesPerSplitF32 pages).
 template <int D>
 __global__ __launch_bounds__(256) void decode_partial_f32(AttnArgs a, WorkArgs w) {
   const int wave = uniform(threadIdx.x >> 6);
@@ -233,8 +233,8 @@ __global__ __launch_bounds__(256) void decode_partial_f32(AttnArgs a, WorkArgs w
   const int4 m = w.meta[dr.x];
   const int n_tok = m.w + m.z;
   const int g = a.group;
-  const int pb = s * w.pages_per_split;
-  const int pe = min(pb + w.pages_per_split, dr.w);
+  const int pb = s * kDecodePagesPerSplitF32;
+  const int pe = min(pb + kDecodePagesPerSplitF32, dr.w);
   const int* prow = a.page_table + (size_t)dr.x * a.max_pages;
   const int item = dr.y + j * dr.z + s;
   f32x4 q[D / 16];

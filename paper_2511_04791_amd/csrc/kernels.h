@@ -39,7 +39,8 @@ struct WorkArgs {
   void* merge_out;        // that layer's output
   int32_t n_merge;        // (decode request, query head) pairs
   int32_t n_pitems, n_dreq, max_split, n_ditems;
-  int32_t pages_per_split;
+  int32_t decode_pps;     // pages per bf16 decode item
+  int32_t decode_small;   // bf16 decode items run one workgroup each and merge themselves (decode_rule)
   int32_t decode_cus;   // CUs the decode stream may use (sizes the persistent grid)
   int32_t prefill_id_cap;  // most pages of any prefill request (sizes the LDS page-id table)
   // Prefill key split (bf16, see kPrefillPieceFill): a piece item carries
@@ -62,8 +63,8 @@ struct AppendArgs {
   int32_t h_kv, head_dim, dtype;
 };
 
-// Decode split length in pages (bf16); fixed, so results do not depend on the CU split.
-constexpr int kDecodePagesPerSplit = 32;
+// Decode split length in pages.
+constexpr int kDecodePagesPerSplit = 32;  // bf16, most batches
 constexpr int kDecodePagesPerSplitF32 = 2;
 // Most logical pages of a bf16 decode request (an item's first page is a 22-bit field).
 constexpr long long kMaxDecodePages = (1LL << 22) - 1;
@@ -80,6 +81,32 @@ constexpr int kDecodeQueueStride = 32;  // ints: one 128-byte line per counter
 constexpr int kDecodeSetLines = 2 * kDecodeQueues;
 constexpr int kDecodeSetInts = kDecodeSetLines * kDecodeQueueStride;
 constexpr int kDecodeCounterInts = 2 * kDecodeSetInts;
+
+// How a batch's bf16 decode work is cut, from its items at kDecodePagesPerSplit pages per item and
+// the most pages of a request.  The rule depends on the batch only, so results are the same for
+// every CU split; where two cuts trade the shares against each other, it takes the one that loses on
+// none of them by more than a few per cent.  Decode time of one layer (us), 32 / 8 heads of 128,
+// on 256, 128 and 32 CUs:
+//   one split per request: a workgroup per item wins throughout (contexts of 300 tokens, 64 items
+//     8.8 / 17 / 17 against 20.6 / 24 / 24 streamed; 512 items 18.8 / 29 / 79 against
+//     26.7 / 34 / 91; 4096 items 117 / 175 / 565 against 146 / 203 / 670);
+//   few items: a workgroup per item (contexts of 2048, 64 items 13.4 / 19.0 / 23.5 against
+//     28.0 / 31.5 / 31.5; from 128 items on 32 CUs lose, 37.4 against 34.3);
+//   then half as long items, streamed (128 items 18.6 / 22.2 / 34.6 against 29.1 / 32.9 / 34.3; 256
+//     items 21.5 / 25.2 / 59.7 against 30.7 / 34.8 / 59.1; 384 items still gain on 256 CUs, 26.3
+//     against 33.0, but lose 2-4% on 32).
+constexpr int kDecodePagesPerSplitShort = 16;
+constexpr int kSmallMaxItems = 96;
+constexpr int kShortMaxItems = 256;
+struct DecodeRule {
+  int pages_per_split;
+  bool small;  // decode_small_bf16: one workgroup per item
+};
+inline DecodeRule decode_rule(int64_t n_items, int max_pages) {
+  if (max_pages <= kDecodePagesPerSplit || n_items <= kSmallMaxItems) return {kDecodePagesPerSplit, true};
+  if (n_items <= kShortMaxItems) return {kDecodePagesPerSplitShort, false};
+  return {kDecodePagesPerSplit, false};
+}
 
 // Keys a prefill request may attend (its page ids are staged in LDS: 8192 ids, 32 KB).
 constexpr int kMaxPrefillKeys = 131072;

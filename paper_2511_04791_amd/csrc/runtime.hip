@@ -79,6 +79,7 @@ struct StepPlan {
   std::vector<int4> meta, dreq;
   std::vector<int4> ditems;
   int n_items = 0, max_split = 0;
+  DecodeRule decode{};
   size_t off_meta = 0, off_dreq = 0, off_ditems = 0;
 };
 
@@ -89,7 +90,8 @@ struct Plan {
   std::vector<int4> ditems;
   std::vector<StepPlan> ahead;  // look-ahead decode steps 1 .. steps - 1
   int steps = 1;
-  int n_items_decode = 0, max_split = 0, pages_per_split = 0, group = 0, prefill_id_cap = 0;
+  int n_items_decode = 0, max_split = 0, group = 0, prefill_id_cap = 0;
+  DecodeRule decode{};
   int prefill_piece_tiles = 0, n_split_units = 0, n_slots = 0;
   size_t off_meta = 0, off_pitems = 0, off_dreq = 0, off_ditems = 0, off_psplit = 0, off_pcount = 0, off_ppart = 0,
          upload_bytes = 0, total = 0;
@@ -97,11 +99,6 @@ struct Plan {
   // layer's partials survive until the next layer's decode kernel has merged them.
   size_t off_pacc[2] = {0, 0}, off_pml[2] = {0, 0};
 };
-
-// Fixed per dtype, never per split or placement, so results are identical for every CU split.
-int pages_per_split_for(const duet_shape* s) {
-  return s->dtype == DUET_F32 ? kDecodePagesPerSplitF32 : kDecodePagesPerSplit;
-}
 
 // Decode work of the batch's decode requests when each holds `extra` more tokens than seq_meta
 // states: per request (req, item_base, n_split, n_pages), and for bf16 the work items in
@@ -112,23 +109,31 @@ int pages_per_split_for(const duet_shape* s) {
 // last one short.
 void decode_lists(const duet_shape* s, const duet_batch* b, int extra, bool step_rows, bool fill,
                   std::vector<int4>* dreq, std::vector<int4>* ditems, int64_t* n_dreq, int64_t* n_items,
-                  int* max_split) {
-  const int pps = pages_per_split_for(s);
+                  int* max_split, DecodeRule* rule) {
   dreq->clear();
   ditems->clear();
+  auto pages_of = [&](const duet_seq_meta& q) { return (int)(((int64_t)q.cached_len + q.q_len + extra + 15) / 16); };
+  int pps = s->dtype == DUET_F32 ? kDecodePagesPerSplitF32 : kDecodePagesPerSplit;
   *n_dreq = 0;
-  *n_items = 0;
-  *max_split = 0;
+  int64_t items = 0;
+  int max_pages = 0;
   for (int r = 0; r < b->num_reqs; ++r) {
     const duet_seq_meta& q = b->reqs[r];
     if (q.kind != DUET_KIND_DECODE) continue;
-    const int64_t L = (int64_t)q.cached_len + q.q_len + extra;
-    const int n_pages = (int)((L + 15) / 16);
-    const int n_split = (n_pages + pps - 1) / pps;
-    if (fill) dreq->push_back(make_int4(r, (int)*n_items, n_split, n_pages));
-    *n_items += (int64_t)s->num_kv_heads * n_split;
-    *max_split = std::max(*max_split, n_split);
     ++*n_dreq;
+    items += (int64_t)s->num_kv_heads * ((pages_of(q) + pps - 1) / pps);
+    max_pages = std::max(max_pages, pages_of(q));
+  }
+  *rule = s->dtype == DUET_BF16 ? decode_rule(items, max_pages) : DecodeRule{pps, false};
+  pps = rule->pages_per_split;
+  *max_split = (max_pages + pps - 1) / pps;
+  *n_items = 0;
+  for (int r = 0; r < b->num_reqs; ++r) {
+    const duet_seq_meta& q = b->reqs[r];
+    if (q.kind != DUET_KIND_DECODE) continue;
+    const int n_split = (pages_of(q) + pps - 1) / pps;
+    if (fill) dreq->push_back(make_int4(r, (int)*n_items, n_split, pages_of(q)));
+    *n_items += (int64_t)s->num_kv_heads * n_split;
   }
   if (fill && s->dtype == DUET_BF16) {
     ditems->reserve(*n_items);
@@ -161,9 +166,7 @@ void decode_lists(const duet_shape* s, const duet_batch* b, int extra, bool step
 // and their offsets in the workspace.
 void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps, Plan* p, bool fill) {
   const int g = s->num_q_heads / s->num_kv_heads;
-  const int pps = pages_per_split_for(s);
   p->group = g;
-  p->pages_per_split = pps;
   p->prefill_id_cap = 0;
   p->meta.clear();
   p->pitems.clear();
@@ -272,7 +275,7 @@ void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps,
   }
   int64_t n_dreq = 0, n_items = 0;
   int max_split = 0;
-  decode_lists(s, b, 0, false, fill, &p->dreq, &p->ditems, &n_dreq, &n_items, &max_split);
+  decode_lists(s, b, 0, false, fill, &p->dreq, &p->ditems, &n_dreq, &n_items, &max_split, &p->decode);
   p->n_items_decode = (int)n_items;
   p->max_split = max_split;
   size_t off = align_up(kCounterOffset + (size_t)kDecodeCounterInts * sizeof(int32_t));
@@ -304,7 +307,7 @@ void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps,
       }
     }
     int64_t nd = 0, ni = 0;
-    decode_lists(s, b, st, true, fill, &sp.dreq, &sp.ditems, &nd, &ni, &sp.max_split);
+    decode_lists(s, b, st, true, fill, &sp.dreq, &sp.ditems, &nd, &ni, &sp.max_split, &sp.decode);
     sp.n_items = (int)ni;
     max_items = std::max(max_items, ni);
     sp.off_meta = off;
@@ -378,7 +381,7 @@ void append_key(std::vector<uint64_t>* k, const DecodeLaunch& l) {
                         bits(w.pitems), bits(w.dreq), bits(w.pacc), bits(w.pml), bits(w.ditems), bits(w.err),
                         bits(w.work_counter), bits(w.clear_counter), bits(w.merge_pacc), bits(w.merge_pml),
                         bits(w.merge_out), bits(w.n_merge), bits(w.n_pitems), bits(w.n_dreq), bits(w.max_split),
-                        bits(w.n_ditems), bits(w.pages_per_split), bits(w.decode_cus), bits(w.prefill_id_cap),
+                        bits(w.n_ditems), bits(w.decode_small), bits(w.decode_pps), bits(w.decode_cus), bits(w.prefill_id_cap),
                         bits(w.ppart), bits(w.psplit), bits(w.pcount), bits(w.prefill_piece_tiles),
                         bits(p.k_cache), bits(p.v_cache), bits(p.k_new), bits(p.v_new), bits(p.page_table),
                         bits(p.num_phys_pages), bits(p.max_pages), bits(p.h_kv), bits(p.head_dim), bits(p.dtype)};
@@ -618,11 +621,12 @@ void base_args(const duet_ctx* ctx, const duet_shape* shape, const Plan& p, char
   w->err = reinterpret_cast<int32_t*>(ws);
   w->work_counter = reinterpret_cast<int32_t*>(ws + kCounterOffset);
   w->n_ditems = (int)p.ditems.size();
+  w->decode_small = p.decode.small;
+  w->decode_pps = p.decode.pages_per_split;
   w->decode_cus = split.mode == DUET_SPLIT ? split.cus_decode : ctx->num_cus;
   w->n_pitems = (int)p.pitems.size();
   w->n_dreq = (int)p.dreq.size();
   w->max_split = p.max_split;
-  w->pages_per_split = p.pages_per_split;
   w->prefill_id_cap = p.prefill_id_cap;
   w->ppart = reinterpret_cast<float*>(ws + p.off_ppart);
   w->psplit = reinterpret_cast<const int2*>(ws + p.off_psplit);
@@ -707,8 +711,8 @@ int attn_layers(duet_ctx* ctx, const duet_shape* shape, int layers, const void* 
   // bf16 decode defers each layer's split merge into the next layer's partial kernel, whose waves
   // merge once their item queue is empty; partial buffers and counter sets alternate by layer,
   // and one reduce kernel merges the last layer.  The fp32 path merges every layer in its own
-  // reduce kernel.
-  const bool defer = has_decode && shape->dtype == DUET_BF16;
+  // reduce kernel; a small bf16 batch merges inside its one decode kernel.
+  const bool defer = has_decode && shape->dtype == DUET_BF16 && !w.decode_small;
   for (int l = 0; l < layers; ++l) {
     const AttnArgs al = layer_args(l);
     if (has_decode) {
@@ -910,6 +914,8 @@ int attn_lookahead(duet_ctx* ctx, const duet_shape* shape, const void* const* q_
       ws_w.n_dreq = (int)spl.dreq.size();
       ws_w.n_ditems = (int)spl.ditems.size();
       ws_w.max_split = spl.max_split;
+      ws_w.decode_small = spl.decode.small;
+      ws_w.decode_pps = spl.decode.pages_per_split;
     }
     for (int l = 0; l < layers; ++l) {
       const int x = (st - 1) * layers + l;
@@ -1235,6 +1241,8 @@ int block_forward(duet_ctx* ctx, const duet_shape* shape, const duet_block_shape
     wl.n_dreq = (int)spl.dreq.size();
     wl.n_ditems = (int)spl.ditems.size();
     wl.max_split = spl.max_split;
+    wl.decode_small = spl.decode.small;
+    wl.decode_pps = spl.decode.pages_per_split;
     for (int l = 0; l < layers; ++l)
       if ((rc = run_layer(dpart, l, static_cast<__bf16*>(x_ahead[st - 1]), wl, wl.dreq))) return rc;
     if (prof && forked) HIP_TRY(hipEventRecord(ctx->ev_step[st + 1], dpart.st));

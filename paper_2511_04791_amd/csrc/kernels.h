@@ -5,6 +5,8 @@
 
 #include <cstdint>
 
+#include "duet.h"
+
 namespace duet {
 
 // Per-iteration tensors and shape, common to every attention kernel.
@@ -158,6 +160,61 @@ struct QkvSplitArgs {
   int32_t num_reqs, max_pages, h_q, h_kv, head_dim;
   int32_t row0;            // first row of the launch
 };
+
+// Where a row's key and value go: the page that holds its position (-1: an id outside the pool) and
+// the slot in it.  The row's request is found by binary search over the request table, whose q_start
+// rise with the request index; in a look-ahead step, row i is decode request i of the step.
+struct QkvSlot {
+  int page, slot;
+};
+__device__ __forceinline__ QkvSlot qkv_slot(const QkvSplitArgs& s, int row) {
+  int lo = 0, hi = s.num_reqs - 1;  // last request with q_start <= row
+  if (s.dreq) {
+    lo = s.dreq[row].x;
+  } else {
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (s.meta[mid].y <= row) lo = mid;
+      else hi = mid - 1;
+    }
+  }
+  const int4 m = s.meta[lo];
+  const int pos = s.dreq ? m.w : m.w + (row - m.y);
+  const int id = s.page_table[(size_t)lo * s.max_pages + (pos >> 4)];
+  return {id >= 0 && (long long)id < s.num_phys_pages ? id : -1, pos & 15};
+}
+
+// Projections of few rows (gemm_skinny.hip) instead of the library's, for a partition of `rows` rows on
+// `cus` CUs whose layer holds `weight_bytes` of projection weights.  On the whole chip the own kernels
+// win for every size measured up to 64 rows (above).  On a share a CU pulls them at about 30 GB/s,
+// somewhat below the library's kernels, which show once nothing else is slower.  Us per layer, own
+// against the library's, on 128 / 96 / 64 / 32 CUs:
+//   0.44 GB (Llama-3-8B), 16 rows: 183 / 238 / 294 / 492 against 227 / 267 / 282 / 443;
+//                         32 rows: 211 / 282 / 357 / 613 against 274 / 325 / 412 / 649;
+//                         64 rows: 260 / 355 / 454 / 797 against 294 / 329 / 380 / 580;
+//   1.7 GB (Llama-3-70B), 16 rows: 541 / 682 / 887 / 1662 against 526 / 759 / 868 / 1424;
+//   12 MB (16 heads of 64), 64 rows: 72 / 72 / 73 / 83 against 95 / 93 / 94 / 94.
+constexpr int kSkinnyRows = 64;
+inline bool use_skinny(int rows, int cus, size_t weight_bytes) {
+  if (rows < 1 || rows > kSkinnyRows) return false;
+  if (cus == DUET_TOTAL_CUS || weight_bytes <= (size_t)64 << 20) return true;
+  return rows <= kSkinnyRows / 2 && cus >= 96 && weight_bytes <= (size_t)512 << 20;
+}
+struct SkinnyArgs {
+  const __bf16* x;  // [rows, d_in]
+  const __bf16* w;  // [d_in, d_out]
+  float* part;      // [splits, rows, d_out]
+  __bf16 *gu, *act; // gate-up: [rows, 2 m], [rows, m]
+  int32_t rows, d_in, d_out, m, splits, tiles;
+};
+int skinny_splits(int rows, int d_in, int d_out, size_t bytes);
+hipError_t launch_skinny_gemm(const __bf16* x, const __bf16* w, float* part, int rows, int d_in, int d_out, int splits,
+                              hipStream_t s);
+hipError_t launch_skinny_gate_up(const __bf16* x, const __bf16* w, __bf16* gu, __bf16* act, int rows, int d_in, int m,
+                                 hipStream_t s);
+hipError_t launch_residual_norm(const float* part, int splits, __bf16* x, const __bf16* w, __bf16* y, int rows, int d,
+                                float eps, hipStream_t s);
+hipError_t launch_qkv_finish(const float* part, int splits, int rows, __bf16* qkv, const QkvSplitArgs& a, hipStream_t s);
 
 hipError_t launch_rmsnorm(const __bf16* x, const __bf16* w, __bf16* y, int rows, int d, float eps, hipStream_t s);
 hipError_t launch_swiglu(const __bf16* gu, __bf16* a, int rows, int m, hipStream_t s);

@@ -1149,13 +1149,17 @@ int block_forward(duet_ctx* ctx, const duet_shape* shape, const duet_block_shape
     int row0, rows;
     bool decode, prefill;
     void* gemm_ws;
+    int cus;
   };
   std::vector<Part> parts;
   if (!forked) {
-    parts.push_back({order, 0, (int)T, w.n_dreq > 0, w.n_pitems > 0, ws + B.gemm_ws[0]});
+    parts.push_back({order, 0, (int)T, w.n_dreq > 0, w.n_pitems > 0, ws + B.gemm_ws[0], ctx->num_cus});
   } else {
-    if (n_dec > 0) parts.push_back({sd, dec0, n_dec, true, false, ws + B.gemm_ws[0]});
-    if (n_pre > 0) parts.push_back({sp, pre0, n_pre, false, true, ws + B.gemm_ws[1]});
+    const bool spatial = split.mode == DUET_SPLIT;
+    if (n_dec > 0)
+      parts.push_back({sd, dec0, n_dec, true, false, ws + B.gemm_ws[0], spatial ? split.cus_decode : ctx->num_cus});
+    if (n_pre > 0)
+      parts.push_back({sp, pre0, n_pre, false, true, ws + B.gemm_ws[1], spatial ? split.cus_prefill : ctx->num_cus});
     HIP_TRY(hipEventRecord(ctx->ev_fork, order));
     for (const Part& pt : parts) {
       HIP_TRY(hipStreamWaitEvent(pt.st, ctx->ev_fork, 0));
@@ -1172,6 +1176,12 @@ int block_forward(duet_ctx* ctx, const duet_shape* shape, const duet_block_shape
   __bf16* gub = reinterpret_cast<__bf16*>(ws + B.gu);
   __bf16* actb = reinterpret_cast<__bf16*>(ws + B.act);
   const char* msg = nullptr;
+  // The own projection kernels read weights 16 bytes at a time.
+  const size_t weight_bytes = (size_t)d * (d_qkv + d + 3 * (size_t)m) * 2;
+  bool weights_aligned = true;
+  for (int l = 0; l < layers; ++l)
+    for (const void* p : {wts[l].w_qkv, wts[l].w_o, wts[l].w_gate_up, wts[l].w_down})
+      weights_aligned &= reinterpret_cast<uintptr_t>(p) % 16 == 0;
   // One layer of one partition over its rows: xr is its first residual row; the activation
   // buffers use rows [pt.row0, pt.row0 + pt.rows).  Look-ahead steps (dreq != null) index their
   // decode requests from 0, so their q / attention rows are addressed from the partition's first
@@ -1191,8 +1201,19 @@ int block_forward(duet_ctx* ctx, const duet_shape* shape, const duet_block_shape
     al.k_cache = k_l[l];
     al.v_cache = v_l[l];
     al.out = step_dreq ? ab + r0 * d : ab;
-    HIP_TRY(launch_rmsnorm(xr, static_cast<const __bf16*>(wt.attn_norm), h, pt.rows, d, eps, pt.st));
-    if (gemm(h, wt.w_qkv, qkv, d, d_qkv, false)) return fail(DUET_EHIP, "QKV projection: %s", msg);
+    // Few rows: own projection kernels, whose finishing kernels run the operator that follows; the
+    // norm before a layer comes with the layer before it.
+    const bool skinny = weights_aligned && use_skinny(pt.rows, pt.cus, weight_bytes);
+    float* part = static_cast<float*>(pt.gemm_ws);
+    auto project = [&](const __bf16* in, const void* wm, int d_in, int d_out, int* splits) {
+      *splits = skinny_splits(pt.rows, d_in, d_out, kGemmWorkspaceBytes);
+      return launch_skinny_gemm(in, static_cast<const __bf16*>(wm), part, pt.rows, d_in, d_out, *splits, pt.st);
+    };
+    int splits = 0;
+    if (!skinny || l == 0)
+      HIP_TRY(launch_rmsnorm(xr, static_cast<const __bf16*>(wt.attn_norm), h, pt.rows, d, eps, pt.st));
+    if (skinny) HIP_TRY(project(h, wt.w_qkv, d, d_qkv, &splits));
+    else if (gemm(h, wt.w_qkv, qkv, d, d_qkv, false)) return fail(DUET_EHIP, "QKV projection: %s", msg);
     QkvSplitArgs qs;
     qs.qkv = step_dreq ? qkv : qkvb;
     qs.q = static_cast<__bf16*>(const_cast<void*>(al.q));
@@ -1209,13 +1230,23 @@ int block_forward(duet_ctx* ctx, const duet_shape* shape, const duet_block_shape
     qs.h_kv = shape->num_kv_heads;
     qs.head_dim = shape->head_dim;
     qs.row0 = step_dreq ? 0 : pt.row0;
-    HIP_TRY(launch_qkv_split(qs, pt.rows, pt.st));
+    if (skinny) HIP_TRY(launch_qkv_finish(part, splits, pt.rows, qkv, qs, pt.st));
+    else HIP_TRY(launch_qkv_split(qs, pt.rows, pt.st));
     if (pt.decode) {
       HIP_TRY(launch_decode_partial(al, wl, pt.st));
       HIP_TRY(launch_decode_reduce(al, wl, pt.st));
     }
     if (pt.prefill) HIP_TRY(launch_prefill(al, wl, pt.st));
     const __bf16* attn_rows = ab + r0 * d;
+    if (skinny) {
+      const __bf16* next_norm = l + 1 < layers ? static_cast<const __bf16*>(wts[l + 1].attn_norm) : nullptr;
+      HIP_TRY(project(attn_rows, wt.w_o, d, d, &splits));
+      HIP_TRY(launch_residual_norm(part, splits, xr, static_cast<const __bf16*>(wt.ffn_norm), h, pt.rows, d, eps, pt.st));
+      HIP_TRY(launch_skinny_gate_up(h, static_cast<const __bf16*>(wt.w_gate_up), gu, act, pt.rows, d, m, pt.st));
+      HIP_TRY(project(act, wt.w_down, m, d, &splits));
+      HIP_TRY(launch_residual_norm(part, splits, xr, next_norm, h, pt.rows, d, eps, pt.st));
+      return DUET_OK;
+    }
     if (gemm(attn_rows, wt.w_o, xr, d, d, true)) return fail(DUET_EHIP, "output projection: %s", msg);
     HIP_TRY(launch_rmsnorm(xr, static_cast<const __bf16*>(wt.ffn_norm), h, pt.rows, d, eps, pt.st));
     if (gemm(h, wt.w_gate_up, gu, d, 2 * m, false)) return fail(DUET_EHIP, "gate-up projection: %s", msg);
@@ -1230,7 +1261,7 @@ int block_forward(duet_ctx* ctx, const duet_shape* shape, const duet_block_shape
   // Look-ahead decode steps 1 .. steps - 1 (Section 4.3): the decode partition runs every layer
   // again for its requests' next tokens, whose residual rows the caller passed in x_ahead; step s
   // writes its tokens' keys and values at position cached_len + s before attending.
-  const Part dpart = forked ? parts[0] : Part{order, dec0, n_dec, true, false, ws + B.gemm_ws[0]};
+  const Part dpart = forked ? parts[0] : Part{order, dec0, n_dec, true, false, ws + B.gemm_ws[0], ctx->num_cus};
   if (prof && steps > 1 && forked) HIP_TRY(hipEventRecord(ctx->ev_step[1], dpart.st));
   for (int st = 1; st < steps; ++st) {
     const StepPlan& spl = p.ahead[st - 1];

@@ -233,6 +233,13 @@ hipError_t launch_gather(const void* cache, int which, int elem_bytes, int h_kv,
                          int max_pages, long long num_phys, int req, int kv_len, void* out, int32_t* err,
                          hipStream_t s);
 
+// Copies `bytes` (a multiple of 16, as zero_bytes) of host-visible memory to dst, the first zero_bytes
+// of dst as zeros; workgroup b < upload_blocks(bytes) <= kUploadBlocks then writes seq to flags[b].
+constexpr int kUploadBlocks = 64;
+int upload_blocks(size_t bytes);
+hipError_t launch_upload(const void* src, void* dst, size_t zero_bytes, size_t bytes, uint32_t* flags, uint32_t seq,
+                         hipStream_t s);
+
 hipError_t launch_read_probe(const void* buf, size_t bytes, int blocks, unsigned* sink, hipStream_t s);
 size_t read_probe_bytes(size_t bytes, int blocks);
 hipError_t launch_mfma_probe(int blocks, int iters, float* sink, hipStream_t s);

@@ -16,11 +16,13 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstring>
 #include <map>
 #include <mutex>
 #include <new>
+#include <thread>
 #include <unordered_map>
 #include <vector>
 
@@ -66,12 +68,19 @@ static_assert(kScratchBytes == DUET_NOALLOC_SCRATCH_BYTES, "the header states th
     if (e_ != hipSuccess) return fail(DUET_EHIP, "%s: %s", #expr, hipGetErrorString(e_)); \
   } while (0)
 
+// One pinned buffer of work lists: kUploadBlocks flags, then cap bytes.  Its reader is the upload
+// kernel, which sets the flags to seq, or a copy command, which `done` follows.
 struct StagingSlot {
-  void* host = nullptr;
+  char* host = nullptr;
   size_t cap = 0;
   hipEvent_t done = nullptr;
-  bool pending = false;
+  enum { kFree, kKernel, kCopy } reader = kFree;
+  uint32_t seq = 0;
+  int blocks = 0;
+  uint32_t* flags() const { return reinterpret_cast<uint32_t*>(host); }
+  char* data() const { return host + kUploadBlocks * sizeof(uint32_t); }
 };
+static_assert(kUploadBlocks * sizeof(uint32_t) % 16 == 0, "the lists start on a 16-byte boundary");
 
 // Decode work lists of one look-ahead step s >= 1 (its own metadata: decode request r becomes
 // (decode, i, 1, cached_len + s), i = its index among the decode requests).
@@ -494,27 +503,56 @@ int ensure_layer_events(duet_ctx* ctx, int layers) {
   return DUET_OK;
 }
 
+// Waits until the slot's last upload has been read.
+int wait_slot(StagingSlot* slot) {
+  if (slot->reader == StagingSlot::kCopy) {
+    HIP_TRY(hipEventSynchronize(slot->done));
+  } else if (slot->reader == StagingSlot::kKernel) {
+    auto unread = [&] {
+      for (int b = 0; b < slot->blocks; ++b)
+        if (__atomic_load_n(slot->flags() + b, __ATOMIC_ACQUIRE) != slot->seq) return true;
+      return false;
+    };
+    const auto start = std::chrono::steady_clock::now();
+    bool late = false;
+    while (unread()) {
+      if (late) return fail(DUET_EHIP, "an upload of work lists did not run");
+      // Far behind a long queue, or the device has failed: let the runtime say which.
+      if (std::chrono::steady_clock::now() - start > std::chrono::seconds(5)) {
+        HIP_TRY(hipDeviceSynchronize());
+        late = true;
+      }
+      std::this_thread::yield();
+    }
+  }
+  slot->reader = StagingSlot::kFree;
+  return DUET_OK;
+}
+
+int alloc_slot(StagingSlot* slot, size_t cap) {
+  if (slot->host) HIP_TRY(hipHostFree(slot->host));
+  slot->host = nullptr;
+  slot->cap = 0;
+  void* p = nullptr;
+  if (hipHostMalloc(&p, kUploadBlocks * sizeof(uint32_t) + cap, hipHostMallocDefault) != hipSuccess)
+    return fail(DUET_ENOMEM, "pinned staging allocation of %zu bytes failed", cap);
+  slot->host = static_cast<char*>(p);
+  std::memset(p, 0, kUploadBlocks * sizeof(uint32_t));
+  slot->seq = 0;
+  slot->cap = cap;
+  return DUET_OK;
+}
+
 int stage_upload(duet_ctx* ctx, const Plan& p, char* ws, hipStream_t st, bool may_allocate = true) {
   StagingSlot& slot = ctx->slots[ctx->next_slot];
   if (!may_allocate && slot.cap < p.upload_bytes)
     return fail(DUET_EWORKSPACE, "work lists of %zu bytes exceed the %zu bytes of preallocated staging", p.upload_bytes,
                 slot.cap);
   ctx->next_slot = (ctx->next_slot + 1) % kStagingSlots;
-  if (slot.pending) {
-    HIP_TRY(hipEventSynchronize(slot.done));
-    slot.pending = false;
-  }
-  if (slot.cap < p.upload_bytes) {
-    if (slot.host) HIP_TRY(hipHostFree(slot.host));
-    slot.host = nullptr;
-    slot.cap = 0;
-    const size_t cap = std::max<size_t>(p.upload_bytes * 2, 1 << 16);
-    if (hipHostMalloc(&slot.host, cap, hipHostMallocDefault) != hipSuccess)
-      return fail(DUET_ENOMEM, "pinned staging allocation of %zu bytes failed", cap);
-    slot.cap = cap;
-  }
-  char* h = static_cast<char*>(slot.host);
-  std::memset(h, 0, p.off_meta);  // clears the error word and the decode work counters
+  int rc = wait_slot(&slot);
+  if (rc) return rc;
+  if (slot.cap < p.upload_bytes && (rc = alloc_slot(&slot, std::max<size_t>(p.upload_bytes * 2, 1 << 16)))) return rc;
+  char* h = slot.data();
   std::memcpy(h + p.off_meta, p.meta.data(), p.meta.size() * sizeof(int4));
   std::memcpy(h + p.off_pitems, p.pitems.data(), p.pitems.size() * sizeof(int4));
   std::memcpy(h + p.off_dreq, p.dreq.data(), p.dreq.size() * sizeof(int4));
@@ -526,9 +564,21 @@ int stage_upload(duet_ctx* ctx, const Plan& p, char* ws, hipStream_t st, bool ma
     std::memcpy(h + sp.off_dreq, sp.dreq.data(), sp.dreq.size() * sizeof(int4));
     std::memcpy(h + sp.off_ditems, sp.ditems.data(), sp.ditems.size() * sizeof(int4));
   }
+  // A stream that is being captured records a copy, guarded by its event as any copy: the flags
+  // of a captured upload would be set by its replays only.
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  const bool known = hipStreamIsCapturing(st, &capturing) == hipSuccess;
+  if (!known) (void)hipGetLastError();
+  if (known && capturing == hipStreamCaptureStatusNone && reinterpret_cast<uintptr_t>(ws) % 16 == 0) {
+    slot.blocks = upload_blocks(p.upload_bytes);
+    HIP_TRY(launch_upload(h, ws, p.off_meta, p.upload_bytes, slot.flags(), ++slot.seq, st));
+    slot.reader = StagingSlot::kKernel;
+    return DUET_OK;
+  }
+  std::memset(h, 0, p.off_meta);  // the error word and the decode work counters
   HIP_TRY(hipMemcpyAsync(ws, h, p.upload_bytes, hipMemcpyHostToDevice, st));
   HIP_TRY(hipEventRecord(slot.done, st));
-  slot.pending = true;
+  slot.reader = StagingSlot::kCopy;
   return DUET_OK;
 }
 
@@ -1348,9 +1398,8 @@ int duet_init(int device, duet_ctx** out) {
       return cleanup(fail(DUET_EHIP, "hipGetSymbolAddress(scratch): %s", hipGetErrorString(e)));
   }
   for (auto& sl : ctx->slots) {
-    if (hipHostMalloc(&sl.host, kStagingPrealloc, hipHostMallocDefault) != hipSuccess)
-      return cleanup(fail(DUET_ENOMEM, "pinned staging allocation of %zu bytes failed", kStagingPrealloc));
-    sl.cap = kStagingPrealloc;
+    const int rc = alloc_slot(&sl, kStagingPrealloc);
+    if (rc) return cleanup(rc);
   }
   ctx->dev_sink = reinterpret_cast<unsigned*>(ctx->dev_flag) + 16;
   *out = ctx;
@@ -1385,10 +1434,8 @@ int duet_destroy(duet_ctx* ctx) {
     (void)hipStreamDestroy(kv.second);
   }
   for (auto& s : ctx->slots) {
-    if (s.done) {
-      if (s.pending) (void)hipEventSynchronize(s.done);
-      (void)hipEventDestroy(s.done);
-    }
+    (void)wait_slot(&s);
+    if (s.done) (void)hipEventDestroy(s.done);
     if (s.host) (void)hipHostFree(s.host);
   }
   for (auto& e : ctx->prof)

@@ -24,6 +24,7 @@
 #include <algorithm>
 
 #include "kernels.h"
+#include "wave_ops.h"
 
 namespace duet {
 namespace {
@@ -50,10 +51,6 @@ __device__ __forceinline__ uint4 weight_load(const char* p) {
   const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
   return make_uint4(v.x, v.y, v.z, v.w);
 }
-
-// The byte permutes that gather the low (high) halves of two words: (a.lo, b.lo), (a.hi, b.hi).
-__device__ __forceinline__ unsigned lows(unsigned a, unsigned b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
-__device__ __forceinline__ unsigned highs(unsigned a, unsigned b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
 
 // part[split][row][d_out] = x[rows, split's slice of d_in] W  (kSwiglu: gu and act, one split).
 template <int NB, bool kSwiglu>
@@ -232,14 +229,18 @@ __global__ __launch_bounds__(1024) void residual_norm(const float* part, int spl
 }
 
 // Four columns of one row per thread: qkv = bf16(sum of the parts), then the QKV split of the row.
-__global__ __launch_bounds__(256) void qkv_finish(const float* part, int splits, int rows, __bf16* qkv, QkvSplitArgs s) {
+__global__ __launch_bounds__(256) void qkv_finish(const float* part, int splits, __bf16* qkv, QkvSplitArgs s) {
   const int nq = s.h_q * s.head_dim, nk = s.h_kv * s.head_dim, width = nq + 2 * nk;
   const int i = blockIdx.y;
   const int col = 4 * (blockIdx.x * 256 + threadIdx.x);
-  if (col >= width) return;
   const int row = s.row0 + i;
-  const QkvSlot at = qkv_slot(s, row);
-  const f32x4 t = sum_parts(part + (size_t)i * width + col, splits, (size_t)rows * width);
+  // The row's request (whole waves search), then the page and slot of its position.
+  const int r = s.dreq ? s.dreq[row].x : find_request(s.num_reqs, [&](int x) { return s.meta[x].y <= row; });
+  const int4 m = s.meta[r];
+  const int pos = s.dreq ? m.w : m.w + (row - m.y);
+  const int id = s.page_table[(size_t)r * s.max_pages + (pos >> 4)], slot = pos & 15;
+  if (col >= width) return;
+  const f32x4 t = sum_parts(part + (size_t)i * width + col, splits, (size_t)s.rows * width);
   bf16x4 v;
 #pragma unroll
   for (int e = 0; e < 4; ++e) v[e] = static_cast<__bf16>(t[e]);
@@ -248,18 +249,18 @@ __global__ __launch_bounds__(256) void qkv_finish(const float* part, int splits,
     *reinterpret_cast<bf16x4*>(s.q + (size_t)row * nq + col) = v;
     return;
   }
-  if (at.page < 0) {
+  if (!page_ok(id, s.num_phys_pages)) {
     if (col == nq) atomicOr(s.err, 1);
     return;
   }
   const int kv = col - nq;
   const int j = (kv % nk) / s.head_dim, e0 = kv % s.head_dim;
-  const size_t slab = (size_t)at.page * s.h_kv + j;
+  const size_t slab = (size_t)id * s.h_kv + j;
   if (kv < nk) {
-    *reinterpret_cast<bf16x4*>(s.k_cache + (slab * 16 + at.slot) * s.head_dim + e0) = v;
+    *reinterpret_cast<bf16x4*>(s.k_cache + (slab * 16 + slot) * s.head_dim + e0) = v;
   } else {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) s.v_cache[(slab * s.head_dim + e0 + e) * 16 + at.slot] = v[e];
+    for (int e = 0; e < 4; ++e) s.v_cache[(slab * s.head_dim + e0 + e) * 16 + slot] = v[e];
   }
 }
 
@@ -320,9 +321,9 @@ hipError_t launch_residual_norm(const float* part, int splits, __bf16* x, const 
   return hipGetLastError();
 }
 
-hipError_t launch_qkv_finish(const float* part, int splits, int rows, __bf16* qkv, const QkvSplitArgs& a, hipStream_t s) {
+hipError_t launch_qkv_finish(const float* part, int splits, __bf16* qkv, const QkvSplitArgs& a, hipStream_t s) {
   const int width = (a.h_q + 2 * a.h_kv) * a.head_dim;
-  hipLaunchKernelGGL(qkv_finish, dim3((width + 1023) / 1024, rows), dim3(256), 0, s, part, splits, rows, qkv, a);
+  hipLaunchKernelGGL(qkv_finish, dim3((width + 1023) / 1024, a.rows), dim3(256), 0, s, part, splits, qkv, a);
   return hipGetLastError();
 }
 

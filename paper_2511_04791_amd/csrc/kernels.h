@@ -158,31 +158,8 @@ struct QkvSplitArgs {
   long long num_phys_pages;
   int32_t* err;
   int32_t num_reqs, max_pages, h_q, h_kv, head_dim;
-  int32_t row0;            // first row of the launch
+  int32_t row0, rows;      // the launch's rows
 };
-
-// Where a row's key and value go: the page that holds its position (-1: an id outside the pool) and
-// the slot in it.  The row's request is found by binary search over the request table, whose q_start
-// rise with the request index; in a look-ahead step, row i is decode request i of the step.
-struct QkvSlot {
-  int page, slot;
-};
-__device__ __forceinline__ QkvSlot qkv_slot(const QkvSplitArgs& s, int row) {
-  int lo = 0, hi = s.num_reqs - 1;  // last request with q_start <= row
-  if (s.dreq) {
-    lo = s.dreq[row].x;
-  } else {
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (s.meta[mid].y <= row) lo = mid;
-      else hi = mid - 1;
-    }
-  }
-  const int4 m = s.meta[lo];
-  const int pos = s.dreq ? m.w : m.w + (row - m.y);
-  const int id = s.page_table[(size_t)lo * s.max_pages + (pos >> 4)];
-  return {id >= 0 && (long long)id < s.num_phys_pages ? id : -1, pos & 15};
-}
 
 // Projections of few rows (gemm_skinny.hip) instead of the library's, for a partition of `rows` rows on
 // `cus` CUs whose layer holds `weight_bytes` of projection weights.  On the whole chip the own kernels
@@ -214,11 +191,11 @@ hipError_t launch_skinny_gate_up(const __bf16* x, const __bf16* w, __bf16* gu, _
                                  hipStream_t s);
 hipError_t launch_residual_norm(const float* part, int splits, __bf16* x, const __bf16* w, __bf16* y, int rows, int d,
                                 float eps, hipStream_t s);
-hipError_t launch_qkv_finish(const float* part, int splits, int rows, __bf16* qkv, const QkvSplitArgs& a, hipStream_t s);
+hipError_t launch_qkv_finish(const float* part, int splits, __bf16* qkv, const QkvSplitArgs& a, hipStream_t s);
 
 hipError_t launch_rmsnorm(const __bf16* x, const __bf16* w, __bf16* y, int rows, int d, float eps, hipStream_t s);
 hipError_t launch_swiglu(const __bf16* gu, __bf16* a, int rows, int m, hipStream_t s);
-hipError_t launch_qkv_split(const QkvSplitArgs& a, int rows, hipStream_t s);
+hipError_t launch_qkv_split(const QkvSplitArgs& a, hipStream_t s);
 
 hipError_t launch_decode_partial(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
 hipError_t launch_decode_reduce(const AttnArgs& a, const WorkArgs& w, hipStream_t s);

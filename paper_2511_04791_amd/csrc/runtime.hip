@@ -534,7 +534,7 @@ int alloc_slot(StagingSlot* slot, size_t cap) {
   slot->host = nullptr;
   slot->cap = 0;
   void* p = nullptr;
-  if (hipHostMalloc(&p, kUploadBlocks * sizeof(uint32_t) + cap, hipHostMallocDefault) != hipSuccess)
+  if (hipHostMalloc(&p, kUploadBlocks * sizeof(uint32_t) + cap, hipHostMallocCoherent) != hipSuccess)
     return fail(DUET_ENOMEM, "pinned staging allocation of %zu bytes failed", cap);
   slot->host = static_cast<char*>(p);
   std::memset(p, 0, kUploadBlocks * sizeof(uint32_t));
@@ -1280,8 +1280,9 @@ int block_forward(duet_ctx* ctx, const duet_shape* shape, const duet_block_shape
     qs.h_kv = shape->num_kv_heads;
     qs.head_dim = shape->head_dim;
     qs.row0 = step_dreq ? 0 : pt.row0;
-    if (skinny) HIP_TRY(launch_qkv_finish(part, splits, pt.rows, qkv, qs, pt.st));
-    else HIP_TRY(launch_qkv_split(qs, pt.rows, pt.st));
+    qs.rows = pt.rows;
+    if (skinny) HIP_TRY(launch_qkv_finish(part, splits, qkv, qs, pt.st));
+    else HIP_TRY(launch_qkv_split(qs, pt.st));
     if (pt.decode) {
       HIP_TRY(launch_decode_partial(al, wl, pt.st));
       HIP_TRY(launch_decode_reduce(al, wl, pt.st));
@@ -1572,7 +1573,8 @@ int duet_qkv_split(duet_ctx* ctx, const duet_shape* shape, const void* qkv, void
   a.h_kv = shape->num_kv_heads;
   a.head_dim = shape->head_dim;
   a.row0 = 0;
-  HIP_TRY(launch_qkv_split(a, (int)T, st));
+  a.rows = (int)T;
+  HIP_TRY(launch_qkv_split(a, st));
   return DUET_OK;
 }
 

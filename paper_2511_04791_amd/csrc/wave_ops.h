@@ -31,4 +31,25 @@ __device__ __forceinline__ float sum_rows(float x) {
   return __uint_as_float(s32[0]) + __uint_as_float(s32[1]);
 }
 
+// The last request r of [0, n) with before(r), where before(0) holds and before is true up to some
+// request and false from there on.  A whole wave searches 64-ary: one memory round trip up to 64
+// requests, two up to 4096.
+template <typename F>
+__device__ __forceinline__ int find_request(int n, F before) {
+  const int lane = threadIdx.x & 63;
+  int lo = 0, end = n;
+  while (end - lo > 1) {
+    const int step = (end - lo + 63) / 64;
+    const int x = lo + lane * step;
+    const int k = __popcll(__ballot(x < end && before(x)));
+    lo += (max(k, 1) - 1) * step;
+    end = min(end, lo + step);
+  }
+  return lo;
+}
+
+// The byte permutes that gather the low (high) halves of two words: (a.lo, b.lo), (a.hi, b.hi).
+__device__ __forceinline__ unsigned lows(unsigned a, unsigned b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
+__device__ __forceinline__ unsigned highs(unsigned a, unsigned b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+
 }  // namespace duet

@@ -70,7 +70,7 @@ extern "C" {
 #define DUET_KIND_PREFILL 0
 #define DUET_KIND_DECODE 1
 
-#define DUET_AGG 0   /* temporal sharing: both halves on the caller's stream, all CUs */
+#define DUET_AGG 0   /* aggregated: both halves on the caller's stream, all CUs */
 #define DUET_SPLIT 1 /* spatial sharing: decode on cus_decode CUs, prefill on cus_prefill CUs */
 #define DUET_CONCURRENT 2 /* control for measurements: both halves at once on two streams that may
                              each use every CU (concurrency without partitioning); accepted by the
@@ -309,7 +309,8 @@ int duet_workspace_bytes(const duet_shape* shape, const duet_batch* batch, size_
  * [num_phys_pages, h_kv, d, 16] (dim-major pages), page_table [num_reqs, max_pages_per_req]
  * int32, workspace and out [T, h_q, d] are device pointers owned by the caller; batch lives in
  * host memory.  Prefill requests go to the MFMA prefill kernel, decode requests to the split-K
- * decode kernel and its reduce kernel.  AGG runs decode then prefill on `stream` (all CUs).
+ * decode kernel and its reduce kernel.  AGG runs both on `stream` (all CUs), with bf16 in one launch
+ * where that is faster: decode workgroups first, prefill items as CUs come free.
  * SPLIT forks onto two CU-masked streams (decode on the first cus_decode CUs, prefill on the last
  * cus_prefill CUs) and joins back onto `stream`; work enqueued on `stream` before the call is complete before
  * either half starts, and work enqueued after it sees the whole output.  The result is
@@ -351,9 +352,9 @@ int duet_attn_mixed_batch_noalloc(duet_ctx* ctx, const duet_shape* shape, const 
  * num_layers device pointers, each laid out as in duet_attn_mixed_batch.  The work lists are
  * built and uploaded once; with SPLIT each half runs its kernels for every layer back to back on
  * its CU-masked stream (the host enqueues the halves layer by layer, alternating), with one fork
- * and one join per call; AGG runs layer by layer, decode then prefill, on `stream`.  With bf16,
- * layer l's decode split merge runs inside layer l + 1's decode kernel (one reduce kernel per call,
- * after the last layer), so no layer's output is complete before the call returns.  Layer l's
+ * and one join per call; AGG runs layer by layer on `stream`.  With bf16, layer l's decode split merge
+ * runs inside layer l + 1's decode kernel (one reduce kernel per call, after the last layer) unless the
+ * batch has few decode items, so no layer's output is complete before the call's work is.  Layer l's
  * output is bit-identical to duet_attn_mixed_batch on layer l's pointers. */
 int duet_attn_iteration(duet_ctx* ctx, const duet_shape* shape, const void* const* q,
                         const void* const* k_cache, const void* const* v_cache, int64_t num_phys_pages,

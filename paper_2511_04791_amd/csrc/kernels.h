@@ -51,6 +51,7 @@ struct WorkArgs {
   const int2* psplit;         // [split units] (first slot, pieces | key tiles per piece << 16)
   int32_t* pcount;            // [split units] pieces finished; zero before and after every launch
   int32_t prefill_piece_tiles;  // P of the rule below (0: no unit is split)
+  long long prefill_tiles;      // key tiles over all units (bf16)
 };
 
 // One decode step's cache write (look-ahead decode): new key and value rows in, paged cache out.
@@ -200,6 +201,18 @@ hipError_t launch_qkv_split(const QkvSplitArgs& a, hipStream_t s);
 hipError_t launch_decode_partial(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
 hipError_t launch_decode_reduce(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
 hipError_t launch_prefill(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
+// Both bf16 halves of a layer in one launch, where that gains: not when prefill lasts so much longer
+// that decode hardly matters (921,000 key tiles beside 1024 decode items: 0.6% slower in one launch;
+// 65,000 beside 1,100: 5% faster), nor for many small decode items, two of which fit on a CU that
+// runs no prefill (us a layer, one launch against two: 512 new tokens beside 32 items 25 / 34,
+// beside 1600 items 84 / 79; 64 tokens beside 800 items 33 / 32).
+constexpr int kMixedMaxTilesPerItem = 256;
+constexpr int kMixedMaxSmallItems = 512;
+inline bool use_mixed(const WorkArgs& w) {
+  return w.n_ditems > 0 && w.n_pitems > 0 && w.prefill_tiles <= (long long)kMixedMaxTilesPerItem * w.n_ditems &&
+         !(w.decode_small && w.n_ditems > kMixedMaxSmallItems);
+}
+hipError_t launch_mixed(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
 // The fp32 paths of the two launchers above.
 hipError_t launch_decode_partial_f32(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
 hipError_t launch_prefill_f32(const AttnArgs& a, const WorkArgs& w, hipStream_t s);

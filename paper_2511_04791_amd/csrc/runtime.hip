@@ -102,6 +102,7 @@ struct Plan {
   int n_items_decode = 0, max_split = 0, group = 0, prefill_id_cap = 0;
   DecodeRule decode{};
   int prefill_piece_tiles = 0, n_split_units = 0, n_slots = 0;
+  int64_t prefill_tiles = 0;
   size_t off_meta = 0, off_pitems = 0, off_dreq = 0, off_ditems = 0, off_psplit = 0, off_pcount = 0, off_ppart = 0,
          upload_bytes = 0, total = 0;
   // Two buffers of split-K partials: consecutive layers of a call alternate between them, so a
@@ -198,6 +199,7 @@ void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps,
   }
   const int P = bf16 && total_tiles > 0 ? prefill_piece_tiles_for(total_tiles) : 0;
   p->prefill_piece_tiles = P;
+  p->prefill_tiles = bf16 ? total_tiles : 0;
   // Units longer than 1.5 P: n pieces of equal length (the last may be shorter), none empty.
   auto pieces_of = [&](int nt) { return P > 0 && 2 * nt > 3 * P ? (nt + P - 1) / P : 1; };
   // Tail split: when the whole units (those the rule above leaves in one piece) number more than
@@ -391,7 +393,7 @@ void append_key(std::vector<uint64_t>* k, const DecodeLaunch& l) {
                         bits(w.work_counter), bits(w.clear_counter), bits(w.merge_pacc), bits(w.merge_pml),
                         bits(w.merge_out), bits(w.n_merge), bits(w.n_pitems), bits(w.n_dreq), bits(w.max_split),
                         bits(w.n_ditems), bits(w.decode_small), bits(w.decode_pps), bits(w.decode_cus), bits(w.prefill_id_cap),
-                        bits(w.ppart), bits(w.psplit), bits(w.pcount), bits(w.prefill_piece_tiles),
+                        bits(w.ppart), bits(w.psplit), bits(w.pcount), bits(w.prefill_piece_tiles), bits(w.prefill_tiles),
                         bits(p.k_cache), bits(p.v_cache), bits(p.k_new), bits(p.v_new), bits(p.page_table),
                         bits(p.num_phys_pages), bits(p.max_pages), bits(p.h_kv), bits(p.head_dim), bits(p.dtype)};
   k->insert(k->end(), std::begin(f), std::end(f));
@@ -682,6 +684,7 @@ void base_args(const duet_ctx* ctx, const duet_shape* shape, const Plan& p, char
   w->psplit = reinterpret_cast<const int2*>(ws + p.off_psplit);
   w->pcount = reinterpret_cast<int32_t*>(ws + p.off_pcount);
   w->prefill_piece_tiles = p.prefill_piece_tiles;
+  w->prefill_tiles = p.prefill_tiles;
 }
 
 // A masked stream the context already holds (no creation): the no-allocation path's lookup.
@@ -763,6 +766,9 @@ int attn_layers(duet_ctx* ctx, const duet_shape* shape, int layers, const void* 
   // and one reduce kernel merges the last layer.  The fp32 path merges every layer in its own
   // reduce kernel; a small bf16 batch merges inside its one decode kernel.
   const bool defer = has_decode && shape->dtype == DUET_BF16 && !w.decode_small;
+  // Aggregated, a layer's two halves are one launch (attn_mixed.hip); per-kernel profiling keeps them
+  // apart.
+  const bool mixed = !forked && !prof && shape->dtype == DUET_BF16 && use_mixed(w);
   for (int l = 0; l < layers; ++l) {
     const AttnArgs al = layer_args(l);
     if (has_decode) {
@@ -781,14 +787,14 @@ int attn_layers(duet_ctx* ctx, const duet_shape* shape, int layers, const void* 
         }
       }
       if (prof) HIP_TRY(hipEventRecord(ctx->ev_dec[3 * l], sd));
-      HIP_TRY(launch_decode_partial(al, wl, sd));
+      HIP_TRY(mixed ? launch_mixed(al, wl, sd) : launch_decode_partial(al, wl, sd));
       if (prof) HIP_TRY(hipEventRecord(ctx->ev_dec[3 * l + 1], sd));
       if (!defer || l == layers - 1) {
         HIP_TRY(launch_decode_reduce(al, wl, sd));
         if (prof) HIP_TRY(hipEventRecord(ctx->ev_dec[3 * l + 2], sd));
       }
     }
-    if (has_prefill) {
+    if (has_prefill && !mixed) {
       if (prof) HIP_TRY(hipEventRecord(ctx->ev_pre[2 * l], sp));
       HIP_TRY(launch_prefill(al, w, sp));
       if (prof) HIP_TRY(hipEventRecord(ctx->ev_pre[2 * l + 1], sp));
@@ -1283,11 +1289,11 @@ int block_forward(duet_ctx* ctx, const duet_shape* shape, const duet_block_shape
     qs.rows = pt.rows;
     if (skinny) HIP_TRY(launch_qkv_finish(part, splits, qkv, qs, pt.st));
     else HIP_TRY(launch_qkv_split(qs, pt.st));
-    if (pt.decode) {
-      HIP_TRY(launch_decode_partial(al, wl, pt.st));
-      HIP_TRY(launch_decode_reduce(al, wl, pt.st));
-    }
-    if (pt.prefill) HIP_TRY(launch_prefill(al, wl, pt.st));
+    const bool mixed = pt.decode && pt.prefill && use_mixed(wl);
+    if (mixed) HIP_TRY(launch_mixed(al, wl, pt.st));
+    else if (pt.decode) HIP_TRY(launch_decode_partial(al, wl, pt.st));
+    if (pt.decode) HIP_TRY(launch_decode_reduce(al, wl, pt.st));
+    if (pt.prefill && !mixed) HIP_TRY(launch_prefill(al, wl, pt.st));
     const __bf16* attn_rows = ab + r0 * d;
     if (skinny) {
       const __bf16* next_norm = l + 1 < layers ? static_cast<const __bf16*>(wts[l + 1].attn_norm) : nullptr;

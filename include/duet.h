@@ -297,7 +297,7 @@ duet_model* duet_ctx_model(duet_ctx* ctx);
  * and batch: an error word, the decode work-queue counters, metadata, work lists, two buffers
  * of decode split-K partials (consecutive layers alternate between them) and the partial states
  * of prefill pieces (bf16: a prefill unit whose causal key range is long against the batch's
- * total runs as several pieces over runs of its keys, merged by the last one to finish, and when
+ * total runs as several pieces over runs of its keys, merged afterwards, and when
  * a batch has at least 512 whole units its 256 shortest run as 4 pieces each; at most 512 + 1024
  * pieces write a partial, 128 KiB each at head_dim 128).  The layers of a call share all of
  * it, so the size does not depend on shape->num_layers.  Host only. */
@@ -331,7 +331,7 @@ int duet_attn_mixed_batch(duet_ctx* ctx, const duet_shape* shape, const void* q,
  * workspace is a file-scope device array of DUET_NOALLOC_SCRATCH_BYTES held by each device the
  * library runs on until the process ends; the call allocates nothing (no device or pinned memory,
  * no streams, no events).  Batches whose work lists and partials need more return
- * DUET_EWORKSPACE, as do work lists beyond the 1 MiB of pinned staging duet_init preallocates.
+ * DUET_EWORKSPACE, as do work lists beyond the 2 MiB of pinned staging duet_init preallocates.
  * Under DUET_SPLIT or DUET_CONCURRENT the CU-masked streams must already exist: one earlier call
  * of duet_attn_mixed_batch or duet_attn_iteration with the same split creates them (the context
  * keeps the streams of its most recently used split or mode); otherwise DUET_EINVAL.  Profiling
@@ -340,7 +340,7 @@ int duet_attn_mixed_batch(duet_ctx* ctx, const duet_shape* shape, const void* q,
  * zero): calls that overlap on one device, from any context or thread, race.  Page ids outside
  * the pool are never dereferenced; the error word they set lives in the scratch and is not
  * reported. */
-#define DUET_NOALLOC_SCRATCH_BYTES (64u << 20)
+#define DUET_NOALLOC_SCRATCH_BYTES (66u << 20)
 int duet_attn_mixed_batch_noalloc(duet_ctx* ctx, const duet_shape* shape, const void* q, const void* k_cache,
                                   const void* v_cache, int64_t num_phys_pages, const int32_t* page_table,
                                   int32_t max_pages_per_req, const duet_batch* batch, duet_cu_split split, void* out,

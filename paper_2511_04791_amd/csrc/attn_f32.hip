@@ -147,10 +147,9 @@ __global__ __launch_bounds__(64 * kF32Waves) void prefill_f32(AttnArgs a, WorkAr
   const int lane = threadIdx.x & 63;
   const int col = lane & 15, quad = lane >> 4;
   constexpr int kBlocks = kPrefillRows / kF32Rows;
-  const int4 it = w.pitems[blockIdx.x / kBlocks];  // (req, query head, first row, 0)
-  const int r = it.x, h = it.y, row0 = it.z + kF32Rows * (blockIdx.x % kBlocks);
-  const int4 m = w.meta[r];
-  const int q_start = m.y, q_len = m.z, c = m.w;
+  const PrefillItem it = w.pitems[blockIdx.x / kBlocks];
+  const int r = it.req, h = it.head, row0 = it.row0 + kF32Rows * (blockIdx.x % kBlocks);
+  const int q_start = it.q_start, q_len = it.q_len, c = it.cached_len;
   if (row0 >= q_len) return;
   const int j = h / a.group;
   const int qi = row0 + col;

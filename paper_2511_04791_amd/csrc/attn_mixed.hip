@@ -100,7 +100,8 @@ hipError_t launch_nh(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_mixed(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
-  return a.head_dim == 128 ? launch_nh<128>(a, w, s) : launch_nh<64>(a, w, s);
+  const hipError_t e = a.head_dim == 128 ? launch_nh<128>(a, w, s) : launch_nh<64>(a, w, s);
+  return e != hipSuccess ? e : launch_prefill_merge(a, w, s);
 }
 
 }  // namespace duet

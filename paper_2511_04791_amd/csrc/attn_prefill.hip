@@ -24,9 +24,9 @@
 //
 // A unit with a long key range may run as several pieces, each over a run of its key tiles
 // (kernels.h).  A piece keeps the same per-row state as a whole unit (reference max, denominator,
-// unnormalised O^T) and stores it; the last piece of the unit to finish combines the stored
-// states in piece order, m = max(m_a, m_b), O = 2^(m_a - m) O_a + 2^(m_b - m) O_b (likewise the
-// denominator), and writes the normalised rows.  Inside a piece a row may see no key at all
+// unnormalised O^T) and stores it.  Of few pieces the last to finish combines the stored states in
+// piece order, m = max(m_a, m_b), O = 2^(m_a - m) O_a + 2^(m_b - m) O_b (likewise the
+// denominator), and writes the normalised rows; of more a merge kernel does.  Inside a piece a row may see no key at all
 // (its position lies before the piece's first key): its state stays (-inf, 0, 0).
 #include <hip/hip_runtime.h>
 
@@ -45,6 +45,80 @@ template <int D, int NH>
 __global__ __launch_bounds__(kThreads, 1) void prefill_bf16(AttnArgs a, WorkArgs w) {
   extern __shared__ __attribute__((aligned(16))) __bf16 lds[];
   prefill_unit<D, NH>(a, w, blockIdx.x, lds);
+}
+
+// Merges the pieces of every unit of more than kPrefillSelfMerge: one wave per (unit, wave of the unit,
+// 32 dims), four pieces in flight, against the common max, sums in piece order.
+template <int D, int NH>
+__global__ __launch_bounds__(256) void prefill_merge(AttnArgs a, WorkArgs w) {
+  constexpr int NO = D / 32;
+  constexpr int WPH = kWaves / NH;
+  const int lane = threadIdx.x & 63, hh = lane >> 5;
+  const int job = 4 * blockIdx.x + uniform(threadIdx.x >> 6);
+  const int unit = job / (kWaves * NO), wave = job / NO % kWaves, n = job % NO;
+  if (unit >= w.n_punits) return;
+  const PrefillUnit u = w.punits[unit];
+  const int wrow0 = u.row0 + 32 * (wave % WPH);
+  if (wrow0 >= u.q_len) return;
+  const float2* const slot = reinterpret_cast<const float2*>(w.ppart) + (size_t)u.slot * kSlotPairs<D>;
+  const float2* const o = slot + (size_t)(wave * NO + n) * 8 * 64 + lane;
+  const float2* const ml = slot + (size_t)kThreads * (D / 4) + (size_t)wave * 64 + lane;
+  float m = -INFINITY;
+#pragma unroll 8
+  for (int p = 0; p < u.pieces; ++p) m = fmaxf(m, ml[p * kSlotPairs<D>].x);
+  float den = 0.f, num[16];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) num[v] = 0.f;
+  for (int p0 = 0; p0 < u.pieces; p0 += 4) {
+    float2 s[4], x[4][8];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {  // pieces past the last re-read it
+      const size_t at = (size_t)min(p0 + k, u.pieces - 1) * kSlotPairs<D>;
+      s[k] = ml[at];
+#pragma unroll
+      for (int v2 = 0; v2 < 8; ++v2) x[k][v2] = o[at + v2 * 64];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (p0 + k >= u.pieces) break;
+      // A piece whose keys all lie past a row's position holds (-inf, 0, 0) for it: weight 0.
+      const float wgt = fast_exp2(s[k].x - m);
+      den += wgt * s[k].y;
+#pragma unroll
+      for (int v2 = 0; v2 < 8; ++v2) {
+        num[2 * v2] += wgt * x[k][v2].x;
+        num[2 * v2 + 1] += wgt * x[k][v2].y;
+      }
+    }
+  }
+  const float inv = 1.0f / pair_sum(den);
+  const int qi = wrow0 + (lane & 31);
+  if (qi >= u.q_len) return;
+  __bf16* op = reinterpret_cast<__bf16*>(a.out) + ((size_t)(u.q_start + qi) * a.h_q + u.head + wave / WPH) * D + 32 * n + 4 * hh;
+#pragma unroll
+  for (int g4 = 0; g4 < 4; ++g4) {
+    __bf16 o4[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o4[e] = static_cast<__bf16>(num[4 * g4 + e] * inv);
+    *reinterpret_cast<uint2*>(op + 8 * g4) = __builtin_bit_cast(uint2, o4);
+  }
+}
+
+template <int D, int NH>
+hipError_t launch_merge(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
+  const int jobs = w.n_punits * kWaves * (D / 32);
+  hipLaunchKernelGGL((prefill_merge<D, NH>), dim3((jobs + 3) / 4), dim3(256), 0, s, a, w);
+  return hipGetLastError();
+}
+
+template <int D>
+hipError_t launch_merge_nh(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
+  switch (prefill_heads_per_unit(a.group)) {
+    case 1: return launch_merge<D, 1>(a, w, s);
+    case 2: return launch_merge<D, 2>(a, w, s);
+    case 4: return launch_merge<D, 4>(a, w, s);
+    default: return launch_merge<D, 8>(a, w, s);
+  }
 }
 
 template <int D, int NH>
@@ -89,12 +163,20 @@ int prefill_piece_tiles_for(long long total_tiles) {
   return (int)std::max<long long>(kPrefillPieceMinTiles, even);
 }
 
-size_t prefill_slot_bytes(int head_dim) { return (size_t)kThreads * (head_dim / 2 + 2) * sizeof(float); }
+size_t prefill_slot_bytes(int head_dim) {
+  return (head_dim == 128 ? kSlotPairs<128> : kSlotPairs<64>) * sizeof(float2);
+}
 
 hipError_t launch_prefill(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
   if (w.n_pitems == 0) return hipSuccess;
-  if (a.dtype == 0) return a.head_dim == 128 ? launch_bf16_nh<128>(a, w, s) : launch_bf16_nh<64>(a, w, s);
-  return launch_prefill_f32(a, w, s);
+  if (a.dtype != 0) return launch_prefill_f32(a, w, s);
+  const hipError_t e = a.head_dim == 128 ? launch_bf16_nh<128>(a, w, s) : launch_bf16_nh<64>(a, w, s);
+  return e != hipSuccess ? e : launch_prefill_merge(a, w, s);
+}
+
+hipError_t launch_prefill_merge(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
+  if (w.n_punits == 0) return hipSuccess;
+  return a.head_dim == 128 ? launch_merge_nh<128>(a, w, s) : launch_merge_nh<64>(a, w, s);
 }
 
 }  // namespace duet

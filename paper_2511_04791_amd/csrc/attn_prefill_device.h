@@ -66,6 +66,11 @@ struct PrefillSmem {
   static size_t bytes(int id_cap) { return kTileBytes + (((size_t)id_cap + 3) & ~(size_t)3) * sizeof(int); }
 };
 
+// A piece's partial state, in float pairs: O as [wave][n][v / 2][lane] (n: 32 dims, v: the lane's 16
+// accumulators of them), then (reference max, this lane's denominator) as [wave][lane].
+template <int D>
+constexpr size_t kSlotPairs = (size_t)kThreads * (D / 4 + 1);
+
 // Work item `index` of the list, by one workgroup of kThreads threads; lds: PrefillSmem bytes.
 template <int D, int NH>
 __device__ __forceinline__ void prefill_unit(const AttnArgs& a, const WorkArgs& w, int index, __bf16* const lds) {
@@ -81,13 +86,12 @@ __device__ __forceinline__ void prefill_unit(const AttnArgs& a, const WorkArgs& 
   const int wave = uniform(tid >> 6);
   const int lane = tid & 63;
   const int hh = lane >> 5;
-  const int4 it = w.pitems[index];  // (req, first query head, q_row0, piece)
-  const int r = it.x, h = it.y + wave / WPH, q_row0 = it.z;
-  const int4 m = w.meta[r];
-  const int q_start = m.y, q_len = m.z, c = m.w;
+  const PrefillItem it = w.pitems[index];
+  const int r = it.req, h = it.head + wave / WPH, q_row0 = it.row0;
+  const int q_start = it.q_start, q_len = it.q_len, c = it.cached_len;
   const int L = c + q_len;
   const int n_pages = (L + 15) >> 4;
-  const int j = it.y / a.group;
+  const int j = it.head / a.group;
 
   const int wrow0 = q_row0 + 32 * (wave % WPH);
   const int qi = wrow0 + (lane & 31);
@@ -105,15 +109,8 @@ __device__ __forceinline__ void prefill_unit(const AttnArgs& a, const WorkArgs& 
     }
   }
 
-  // Key tiles [kt0, kt1) of the unit: all of them, or one piece's run.
-  const int unit_tiles = (c + min(q_row0 + QB - 1, q_len - 1)) / BN + 1;
-  const int piece = it.w & ((1 << kPrefillPieceBits) - 1);
-  const int split_unit = (it.w >> kPrefillPieceBits) - 1;  // -1: whole unit
-  // (first slot, pieces | tiles per piece << 16)
-  const int2 su = split_unit >= 0 ? w.psplit[split_unit] : make_int2(0, 1 | (unit_tiles << 16));
-  const int n_pieces = su.y & 0xffff, piece_tiles = su.y >> 16;
-  const int kt0 = piece * piece_tiles;
-  const int kt1 = min(unit_tiles, kt0 + piece_tiles);
+  // Key tiles [kt0, kt1): all of the unit's, or one piece's run.
+  const int kt0 = it.tiles & 0xffff, kt1 = it.tiles >> 16;
   const int w_tiles = wrow0 < q_len ? (c + min(wrow0 + 31, q_len - 1)) / BN + 1 : 0;
   const int w_first_pos = c + wrow0;
 
@@ -355,19 +352,32 @@ __device__ __forceinline__ void prefill_unit(const AttnArgs& a, const WorkArgs& 
   }
 
   if (bad) atomicOr(w.err, 1);
-  if (split_unit >= 0) {
-    // Slot layout, in float pairs: O as [wave][n][v / 2][lane], then (m, l) as [wave][lane]; every
-    // lane stores and later loads exactly its own registers.  The slots are written and read with
-    // relaxed device-scope atomic accesses (coherent across the XCDs' L2 caches without the
-    // whole-cache write-back and invalidation a device-scope fence costs every workgroup on the
-    // XCD); a piece counts itself only once its stores have completed.
-    constexpr size_t kSlotPairs = (size_t)kThreads * (D / 4 + 1);
+  if (it.slot >= 0) {
+    // A piece: its state goes to its slot (piece_slot in kernels.h).
+    const int slot = it.slot & 0xffff, piece = it.slot >> 16 & 0xff, n_pieces = it.slot >> 24;
     typedef unsigned long long u64;
-    auto o_at = [&](int slot) {
-      return reinterpret_cast<u64*>(w.ppart) + (size_t)slot * kSlotPairs + (size_t)wave * NO * 8 * 64 + lane;
+    const int slot0 = slot - piece;
+    if (n_pieces == 0) {
+      // The merge kernel does (waves without rows have no state).
+      if (wrow0 >= q_len) return;
+      float2* const base = reinterpret_cast<float2*>(w.ppart) + (size_t)slot * kSlotPairs<D>;
+      float2* const o = base + (size_t)wave * NO * 8 * 64 + lane;
+#pragma unroll
+      for (int n = 0; n < NO; ++n)
+#pragma unroll
+        for (int v2 = 0; v2 < 8; ++v2) o[(n * 8 + v2) * 64] = make_float2(oacc[n][2 * v2], oacc[n][2 * v2 + 1]);
+      base[(size_t)kThreads * (D / 4) + (size_t)wave * 64 + lane] = make_float2(m_ref, l_run);
+      return;
+    }
+    // The last piece of the unit to finish does.  The slots are written and read with relaxed
+    // device-scope atomic accesses (coherent across the XCDs' L2 caches without the whole-cache
+    // write-back and invalidation a device-scope fence costs every workgroup on the XCD); a piece
+    // counts itself only once its stores have completed.
+    auto o_at = [&](int at) {
+      return reinterpret_cast<u64*>(w.ppart) + (size_t)at * kSlotPairs<D> + (size_t)wave * NO * 8 * 64 + lane;
     };
-    auto ml_at = [&](int slot) {
-      return reinterpret_cast<u64*>(w.ppart) + (size_t)slot * kSlotPairs + (size_t)kThreads * (D / 4) +
+    auto ml_at = [&](int at) {
+      return reinterpret_cast<u64*>(w.ppart) + (size_t)at * kSlotPairs<D> + (size_t)kThreads * (D / 4) +
              (size_t)wave * 64 + lane;
     };
     auto pack = [](float x, float y) {
@@ -376,22 +386,22 @@ __device__ __forceinline__ void prefill_unit(const AttnArgs& a, const WorkArgs& 
     auto lo = [](u64 v) { return __uint_as_float((unsigned)v); };
     auto hi = [](u64 v) { return __uint_as_float((unsigned)(v >> 32)); };
     {
-      u64* o = o_at(su.x + piece);
+      u64* o = o_at(slot);
 #pragma unroll
       for (int n = 0; n < NO; ++n)
 #pragma unroll
         for (int v2 = 0; v2 < 8; ++v2)
           __hip_atomic_store(o + (n * 8 + v2) * 64, pack(oacc[n][2 * v2], oacc[n][2 * v2 + 1]), __ATOMIC_RELAXED,
                              __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(ml_at(su.x + piece), pack(m_ref, l_run), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(ml_at(slot), pack(m_ref, l_run), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's slot stores have completed
     __syncthreads();
     // The arrival flag reuses the page-id table's first word: no id is read after the key loop.
     if (tid == 0) {
-      const int done = atomicAdd(w.pcount + split_unit, 1) + 1;
+      const int done = atomicAdd(w.pcount + slot0, 1) + 1;
       ids[0] = done == n_pieces;
-      if (done == n_pieces) atomicExch(w.pcount + split_unit, 0);  // ready for the next launch
+      if (done == n_pieces) atomicExch(w.pcount + slot0, 0);  // ready for the next launch
     }
     __syncthreads();
     if (!ids[0]) return;
@@ -409,8 +419,8 @@ __device__ __forceinline__ void prefill_unit(const AttnArgs& a, const WorkArgs& 
 #pragma unroll
         for (int n = 0; n < NO; ++n) op[n] = own[n];
       } else {
-        const u64* o = o_at(su.x + pc);
-        ml = __hip_atomic_load(ml_at(su.x + pc), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const u64* o = o_at(slot0 + pc);
+        ml = __hip_atomic_load(ml_at(slot0 + pc), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
         for (int n = 0; n < NO; ++n)
 #pragma unroll

@@ -22,10 +22,28 @@ struct AttnArgs {
   float scale_log2;      // log2(e) / sqrt(d): scores are kept in base-2 units
 };
 
+// One prefill workgroup's work: query rows row0 .. of a request for some heads from `head` on (bf16: all
+// heads of the unit; fp32: one), over key tiles [tiles & 0xffff, tiles >> 16).  Everything a
+// workgroup needs to start, in one read.
+struct PrefillItem {
+  int32_t req, head, row0;
+  int32_t slot;  // -1: a whole unit, else piece_slot of a piece
+  int32_t q_start, q_len, cached_len;
+  uint32_t tiles;
+};
+// A piece's slot; for a unit that merges itself also the piece's index in it (its pieces have
+// consecutive slots) and the number of pieces (0: the merge kernel merges them).
+inline int32_t piece_slot(int slot, int piece, int pieces_to_merge) { return slot | piece << 16 | pieces_to_merge << 24; }
+// A prefill unit whose pieces the merge kernel merges: slots slot .. slot + pieces - 1.
+struct PrefillUnit {
+  int32_t slot, pieces;
+  int32_t req, head, row0, q_start, q_len, pad;
+};
+
 // Work lists and scratch that live in the caller's workspace.
 struct WorkArgs {
   const int4* meta;     // [R]  (kind, q_start, q_len, cached_len)
-  const int4* pitems;   // [NP] prefill tiles (req, q_head, q_row0, 0), heaviest first
+  const PrefillItem* pitems;  // [NP] heaviest first
   const int4* dreq;     // [RD] decode requests (req, item_base, n_split, n_pages)
   float* pacc;          // [ND, group, d]  unnormalised split-K partial outputs
   float* pml;           // [ND, group, 2]  (running max in base-2 units, softmax denominator)
@@ -45,12 +63,11 @@ struct WorkArgs {
   int32_t decode_small;   // bf16 decode items run one workgroup each and merge themselves (decode_rule)
   int32_t decode_cus;   // CUs the decode stream may use (sizes the persistent grid)
   int32_t prefill_id_cap;  // most pages of any prefill request (sizes the LDS page-id table)
-  // Prefill key split (bf16, see kPrefillPieceFill): a piece item carries
-  // ((split unit + 1) << kPrefillPieceBits) | piece in its w field (0: a whole unit).
+  // Prefill key split (bf16, see kPrefillPieceFill).
   float* ppart;               // [slots] partial state of every piece: unnormalised O, running max, denominator
-  const int2* psplit;         // [split units] (first slot, pieces | key tiles per piece << 16)
-  int32_t* pcount;            // [split units] pieces finished; zero before and after every launch
-  int32_t prefill_piece_tiles;  // P of the rule below (0: no unit is split)
+  int32_t* pcount;            // [slots] pieces finished, at the unit's first slot; zero before and after every launch
+  const PrefillUnit* punits;  // [n_punits] units for the merge kernel
+  int32_t n_punits;
   long long prefill_tiles;      // key tiles over all units (bf16)
 };
 
@@ -130,8 +147,9 @@ int prefill_rows_per_unit(int group, int dtype);
 // cached prefix (few units, each long) still fills the CUs.  Every piece pays a fixed start-up
 // cost and a partial-state round trip, so units within 1.5 P of the share stay whole.  P depends
 // on the batch only, never on the CU split, so results are the same for every split.  Each piece
-// writes its partial state to a slot; the piece that finishes last (an arrival counter per unit)
-// merges the slots in piece order and writes the output.  Split units number at most
+// writes its partial state to a slot.  Of up to kPrefillSelfMerge pieces the last to finish (a
+// counter per unit) merges the slots in piece order and writes the output; the slots of more
+// pieces are merged by a kernel of their own.  Split units number at most
 // T / P <= kPrefillPieceFill and their slots at most 2 T / P, plus the tail split's below
 // (kPrefillPieceFill units, kPrefillTailPieces slots each).
 constexpr int kPrefillPieceMinTiles = 8;
@@ -142,7 +160,16 @@ constexpr int kPrefillPieceFill = 256;
 // (one workgroup per CU leaves up to one unit's length idle at the end otherwise).
 constexpr int kPrefillTailPieces = 4;
 constexpr int kPrefillTailMinTiles = 16;
-constexpr int kPrefillPieceBits = 12;  // piece index field of an item's w (pieces <= 4095)
+// One workgroup reads a piece's 128 KiB in about 2 us, whatever the other CUs do; a kernel reads all of
+// them on every CU but takes about 10 us with its launch.  One layer (us), merged by the last piece
+// against by a kernel: two pieces (2048 tokens, 32 / 8 heads) 53.5 / 60.5; tail split in four (8192
+// tokens) 513 / 529; five (8 / 1 heads, 1500 tokens after 900) 35.7 / 40.1; eight (4 / 4 heads, 2048
+// after 2048) 42.4 / 33.2; 16 (32 / 8 heads, 16 tokens after 8000) 51.7 / 30.0; 33 (4 / 4 heads, 512
+// after 16384) 88.6 / 44.5.
+constexpr int kPrefillSelfMerge = 6;
+static_assert(kPrefillTailPieces <= kPrefillSelfMerge, "the tail split merges itself");
+static_assert(2 * kPrefillPieceFill + kPrefillPieceFill * kPrefillTailPieces <= 0xffff, "a slot fits 16 bits");
+static_assert(kMaxPrefillKeys / kPrefillKeys <= 0xffff, "a tile index fits 16 bits");
 int prefill_piece_tiles_for(long long total_tiles);
 size_t prefill_slot_bytes(int head_dim);  // one piece's partial state
 
@@ -201,6 +228,8 @@ hipError_t launch_qkv_split(const QkvSplitArgs& a, hipStream_t s);
 hipError_t launch_decode_partial(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
 hipError_t launch_decode_reduce(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
 hipError_t launch_prefill(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
+// Merges the units that ran as pieces (bf16; launch_prefill and launch_mixed end with it).
+hipError_t launch_prefill_merge(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
 // Both bf16 halves of a layer in one launch, where that gains: not when prefill lasts so much longer
 // that decode hardly matters (921,000 key tiles beside 1024 decode items: 0.6% slower in one launch;
 // 65,000 beside 1,100: 5% faster), nor for many small decode items, two of which fit on a CU that

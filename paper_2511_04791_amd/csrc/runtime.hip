@@ -53,9 +53,9 @@ constexpr size_t kMaxGraphs = 128;    // cached decode-step graphs per context
 // Each device the library runs on holds its own copy until the process ends.  In host code the
 // array's name is not a device address: its address on a device comes from hipGetSymbolAddress
 // (duet_init, with the device current) and is kept in the context.
-constexpr size_t kScratchBytes = size_t(64) << 20;
+constexpr size_t kScratchBytes = size_t(66) << 20;
 // Pinned staging allocated up front for each slot, so that the no-allocation path never grows it.
-constexpr size_t kStagingPrealloc = size_t(1) << 20;
+constexpr size_t kStagingPrealloc = size_t(2) << 20;
 
 inline size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 
@@ -94,16 +94,17 @@ struct StepPlan {
 
 // Work lists of one iteration and where they live in the caller's workspace.
 struct Plan {
-  std::vector<int4> meta, pitems, dreq;
-  std::vector<int2> psplit;  // per split prefill unit: (first partial slot, pieces | tiles per piece << 16)
+  std::vector<int4> meta, dreq;
+  std::vector<PrefillItem> pitems;
+  std::vector<PrefillUnit> punits;
   std::vector<int4> ditems;
   std::vector<StepPlan> ahead;  // look-ahead decode steps 1 .. steps - 1
   int steps = 1;
   int n_items_decode = 0, max_split = 0, group = 0, prefill_id_cap = 0;
   DecodeRule decode{};
-  int prefill_piece_tiles = 0, n_split_units = 0, n_slots = 0;
+  int n_punits = 0, n_slots = 0;
   int64_t prefill_tiles = 0;
-  size_t off_meta = 0, off_pitems = 0, off_dreq = 0, off_ditems = 0, off_psplit = 0, off_pcount = 0, off_ppart = 0,
+  size_t off_meta = 0, off_pitems = 0, off_dreq = 0, off_ditems = 0, off_punits = 0, off_pcount = 0, off_ppart = 0,
          upload_bytes = 0, total = 0;
   // Two buffers of split-K partials: consecutive layers of a call alternate between them, so a
   // layer's partials survive until the next layer's decode kernel has merged them.
@@ -181,7 +182,7 @@ void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps,
   p->meta.clear();
   p->pitems.clear();
   p->steps = steps;
-  p->psplit.clear();
+  p->punits.clear();
   const bool bf16 = s->dtype == DUET_BF16;
   // bf16: a unit is nh heads of one group x rows queries; fp32: one head x rows queries.
   const int nh = bf16 ? prefill_heads_per_unit(g) : 1;
@@ -198,7 +199,6 @@ void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps,
     for (int t = 0; t * rows < q.q_len; ++t) total_tiles += (int64_t)block_tiles(q, t) * units;
   }
   const int P = bf16 && total_tiles > 0 ? prefill_piece_tiles_for(total_tiles) : 0;
-  p->prefill_piece_tiles = P;
   p->prefill_tiles = bf16 ? total_tiles : 0;
   // Units longer than 1.5 P: n pieces of equal length (the last may be shorter), none empty.
   auto pieces_of = [&](int nt) { return P > 0 && 2 * nt > 3 * P ? (nt + P - 1) / P : 1; };
@@ -236,10 +236,10 @@ void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps,
     }
   }
   int64_t n_pitems = 0;
-  int n_su = 0, n_slots = 0;
+  int n_pu = 0, n_slots = 0;
   struct Tile {
     int64_t keys;
-    int4 item;
+    PrefillItem item;
   };
   std::vector<Tile> tiles;
   for (int r = 0; r < b->num_reqs; ++r) {
@@ -256,28 +256,35 @@ void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps,
       const int len = (nt + pieces - 1) / pieces;
       pieces = (nt + len - 1) / len;
       n_pitems += (int64_t)pieces * units;
-      if (pieces > 1) {
+      // Unit u's query heads from head(u) on.  Units are ordered so that workgroup index mod 8 follows the
+      // kv head: the units sharing one kv head land on one XCD and share its L2.
+      auto head = [&](int u) { return nh == 1 ? (u % s->num_kv_heads) * g + u / s->num_kv_heads : u * nh; };
+      const int slot0 = n_slots;
+      const bool kernel_merges = pieces > kPrefillSelfMerge;
+      if (kernel_merges) {
         if (fill)
-          for (int u = 0; u < units; ++u) p->psplit.push_back(make_int2(n_slots + u * pieces, pieces | (len << 16)));
-        n_su += units;
-        n_slots += units * pieces;
+          for (int u = 0; u < units; ++u)
+            p->punits.push_back({slot0 + u * pieces, pieces, r, head(u), t * rows, q.q_start, q.q_len, 0});
+        n_pu += units;
       }
+      if (pieces > 1) n_slots += units * pieces;
       if (!fill) continue;
-      // Units ordered so that workgroup index mod 8 follows the kv head: the units sharing one kv
-      // head land on one XCD and share its L2.  Piece pc of every unit of a block, then piece
-      // pc + 1: pieces of equal length stay together through the sort below.
+      // Piece pc of every unit of a block, then piece pc + 1: pieces of equal length stay together
+      // through the sort below.
       for (int pc = 0; pc < pieces; ++pc) {
-        const int64_t keys = pieces > 1 ? (int64_t)std::min(len, nt - pc * len) * kPrefillKeys
+        const int kt1 = std::min(nt, (pc + 1) * len);
+        const int64_t keys = pieces > 1 ? (int64_t)(kt1 - pc * len) * kPrefillKeys
                                         : q.cached_len + std::min(q.q_len, (t + 1) * rows);
         for (int u = 0; u < units; ++u) {
-          const int h = nh == 1 ? (u % s->num_kv_heads) * g + u / s->num_kv_heads : u * nh;
-          const int su = pieces > 1 ? n_su - units + u : -1;
-          tiles.push_back({keys, make_int4(r, h, t * rows, ((su + 1) << kPrefillPieceBits) | (pieces > 1 ? pc : 0))});
+          const int slot = slot0 + u * pieces + pc;
+          tiles.push_back({keys, {r, head(u), t * rows,
+                                  pieces == 1 ? -1 : kernel_merges ? piece_slot(slot, 0, 0) : piece_slot(slot, pc, pieces),
+                                  q.q_start, q.q_len, q.cached_len, (uint32_t)(pc * len) | (uint32_t)kt1 << 16}});
         }
       }
     }
   }
-  p->n_split_units = n_su;
+  p->n_punits = n_pu;
   p->n_slots = n_slots;
   if (fill) {
     std::stable_sort(tiles.begin(), tiles.end(), [](const Tile& x, const Tile& y) { return x.keys > y.keys; });
@@ -293,15 +300,15 @@ void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps,
   p->off_meta = off;
   off = align_up(off + (size_t)b->num_reqs * sizeof(int4));
   p->off_pitems = off;
-  off = align_up(off + (size_t)n_pitems * sizeof(int4));
+  off = align_up(off + (size_t)n_pitems * sizeof(PrefillItem));
   p->off_dreq = off;
   off = align_up(off + (size_t)n_dreq * sizeof(int4));
   p->off_ditems = off;
   off = align_up(off + (s->dtype == DUET_BF16 ? (size_t)n_items * sizeof(int4) : 0));
-  p->off_psplit = off;
-  off = align_up(off + (size_t)n_su * sizeof(int2));
+  p->off_punits = off;
+  off = align_up(off + (size_t)n_pu * sizeof(PrefillUnit));
   p->off_pcount = off;  // zeroed by the upload
-  off = align_up(off + (size_t)n_su * sizeof(int32_t));
+  off = align_up(off + (size_t)n_slots * sizeof(int32_t));
   // Look-ahead steps: each has its own metadata and decode lists; the split-K partials are
   // shared, since the steps run one after another on one stream.
   int64_t max_items = n_items;
@@ -346,8 +353,8 @@ void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps,
 // inside every other block of four balances the engines' work (the 2048-token chunk on 96 CUs:
 // 126 vs 131 us); on all 256 CUs the plain order is kept (the long 70B chunk: 1% faster).  A
 // permutation of whole rounds: every XCD keeps its units.
-void snake_prefill_rounds(std::vector<int4>* items) {
-  std::vector<int4>& v = *items;
+void snake_prefill_rounds(std::vector<PrefillItem>* items) {
+  std::vector<PrefillItem>& v = *items;
   for (size_t b0 = 32; b0 + 32 <= v.size(); b0 += 64)
     for (int a = 0, z = 3; a < z; ++a, --z)
       for (int u = 0; u < 8; ++u) std::swap(v[b0 + 8 * a + u], v[b0 + 8 * z + u]);
@@ -393,7 +400,7 @@ void append_key(std::vector<uint64_t>* k, const DecodeLaunch& l) {
                         bits(w.work_counter), bits(w.clear_counter), bits(w.merge_pacc), bits(w.merge_pml),
                         bits(w.merge_out), bits(w.n_merge), bits(w.n_pitems), bits(w.n_dreq), bits(w.max_split),
                         bits(w.n_ditems), bits(w.decode_small), bits(w.decode_pps), bits(w.decode_cus), bits(w.prefill_id_cap),
-                        bits(w.ppart), bits(w.psplit), bits(w.pcount), bits(w.prefill_piece_tiles), bits(w.prefill_tiles),
+                        bits(w.ppart), bits(w.punits), bits(w.n_punits), bits(w.pcount), bits(w.prefill_tiles),
                         bits(p.k_cache), bits(p.v_cache), bits(p.k_new), bits(p.v_new), bits(p.page_table),
                         bits(p.num_phys_pages), bits(p.max_pages), bits(p.h_kv), bits(p.head_dim), bits(p.dtype)};
   k->insert(k->end(), std::begin(f), std::end(f));
@@ -556,11 +563,11 @@ int stage_upload(duet_ctx* ctx, const Plan& p, char* ws, hipStream_t st, bool ma
   if (slot.cap < p.upload_bytes && (rc = alloc_slot(&slot, std::max<size_t>(p.upload_bytes * 2, 1 << 16)))) return rc;
   char* h = slot.data();
   std::memcpy(h + p.off_meta, p.meta.data(), p.meta.size() * sizeof(int4));
-  std::memcpy(h + p.off_pitems, p.pitems.data(), p.pitems.size() * sizeof(int4));
+  std::memcpy(h + p.off_pitems, p.pitems.data(), p.pitems.size() * sizeof(PrefillItem));
   std::memcpy(h + p.off_dreq, p.dreq.data(), p.dreq.size() * sizeof(int4));
   std::memcpy(h + p.off_ditems, p.ditems.data(), p.ditems.size() * sizeof(int4));
-  std::memcpy(h + p.off_psplit, p.psplit.data(), p.psplit.size() * sizeof(int2));
-  std::memset(h + p.off_pcount, 0, (size_t)p.n_split_units * sizeof(int32_t));
+  std::memcpy(h + p.off_punits, p.punits.data(), p.punits.size() * sizeof(PrefillUnit));
+  std::memset(h + p.off_pcount, 0, (size_t)p.n_slots * sizeof(int32_t));
   for (const StepPlan& sp : p.ahead) {
     std::memcpy(h + sp.off_meta, sp.meta.data(), sp.meta.size() * sizeof(int4));
     std::memcpy(h + sp.off_dreq, sp.dreq.data(), sp.dreq.size() * sizeof(int4));
@@ -665,7 +672,7 @@ void base_args(const duet_ctx* ctx, const duet_shape* shape, const Plan& p, char
   a->scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)shape->head_dim));
   *w = WorkArgs{};
   w->meta = reinterpret_cast<const int4*>(ws + p.off_meta);
-  w->pitems = reinterpret_cast<const int4*>(ws + p.off_pitems);
+  w->pitems = reinterpret_cast<const PrefillItem*>(ws + p.off_pitems);
   w->dreq = reinterpret_cast<const int4*>(ws + p.off_dreq);
   w->pacc = reinterpret_cast<float*>(ws + p.off_pacc[0]);
   w->pml = reinterpret_cast<float*>(ws + p.off_pml[0]);
@@ -681,9 +688,9 @@ void base_args(const duet_ctx* ctx, const duet_shape* shape, const Plan& p, char
   w->max_split = p.max_split;
   w->prefill_id_cap = p.prefill_id_cap;
   w->ppart = reinterpret_cast<float*>(ws + p.off_ppart);
-  w->psplit = reinterpret_cast<const int2*>(ws + p.off_psplit);
+  w->punits = reinterpret_cast<const PrefillUnit*>(ws + p.off_punits);
+  w->n_punits = p.n_punits;
   w->pcount = reinterpret_cast<int32_t*>(ws + p.off_pcount);
-  w->prefill_piece_tiles = p.prefill_piece_tiles;
   w->prefill_tiles = p.prefill_tiles;
 }
 

@@ -74,15 +74,24 @@ def _meta_rows(seq_meta):
 
 
 class _BatchC:
-    """Keeps the ctypes array alive alongside the struct that points into it."""
+    """The batch as the C ABI takes it.  Its ctypes array holds a copy of the rows."""
+    __slots__ = ("rows", "arr", "c")
 
     def __init__(self, seq_meta):
-        rows = _meta_rows(seq_meta)
-        self.rows = rows
-        self.arr = (N.SeqMeta * max(1, len(rows)))()
-        if len(rows):
-            ctypes.memmove(self.arr, rows.ctypes.data, rows.nbytes)
-        self.c = N.Batch(self.arr, len(rows))
+        # The rows as an engine hands them over need no conversion.
+        if not (type(seq_meta) is np.ndarray and seq_meta.dtype == np.int32 and seq_meta.ndim == 2 and
+                seq_meta.shape[1] == 4 and seq_meta.flags.c_contiguous):
+            seq_meta = _meta_rows(seq_meta)
+        n = len(seq_meta)
+        self.rows = seq_meta
+        self.arr = (N.SeqMeta * n).from_buffer_copy(seq_meta) if n else (N.SeqMeta * 1)()
+        self.c = N.Batch(self.arr, n)
+
+    def num_tokens(self) -> int:
+        return sum(self.rows[:, 2].tolist()) if len(self.rows) else 0
+
+    def num_decodes(self) -> int:
+        return self.rows[:, 0].tolist().count(KIND_DECODE) if len(self.rows) else 0
 
 
 class Model:
@@ -237,12 +246,15 @@ def batch_work(batch, shape: AttnShape, kind: int = -1) -> tuple[float, float]:
     return f.value, by.value
 
 
-def workspace_bytes(shape: AttnShape, seq_meta) -> int:
-    b = _BatchC(seq_meta)
+def _workspace_bytes(shape_c: N.Shape, batch: _BatchC) -> int:
     n = ctypes.c_size_t()
-    N.check(N.lib().duet_workspace_bytes(ctypes.byref(_shape_c(shape)), ctypes.byref(b.c), ctypes.byref(n)),
+    N.check(N.lib().duet_workspace_bytes(ctypes.byref(shape_c), ctypes.byref(batch.c), ctypes.byref(n)),
             "duet_workspace_bytes")
     return n.value
+
+
+def workspace_bytes(shape: AttnShape, seq_meta) -> int:
+    return _workspace_bytes(_shape_c(shape), _BatchC(seq_meta))
 
 
 def block_workspace_bytes(shape: AttnShape, block: BlockShape, seq_meta, k_decode_steps: int = 1) -> int:
@@ -351,6 +363,14 @@ def shape_of(q, k_cache, num_layers: int = 1) -> AttnShape:
     return AttnShape(int(q.shape[1]), int(k_cache.shape[1]), int(q.shape[2]), dt, int(k_cache.shape[2]), num_layers)
 
 
+def _stream_of(t, stream) -> ctypes.c_void_p:
+    """The caller's stream, or torch's current one on the tensor's device."""
+    if stream is None:
+        import torch
+        stream = torch.cuda.current_stream(t.device).cuda_stream
+    return ctypes.c_void_p(stream)
+
+
 class Context:
     """A duet_ctx on one GPU: CU-masked stream pool, kernels, probes and its latency model.
 
@@ -390,16 +410,18 @@ class Context:
         return self._ws
 
     @staticmethod
-    def _check_layer(q, k_cache, v_cache, page_table, b):
+    def _check_layer(q, k_cache, v_cache, page_table, b, n_tok=None):
+        """n_tok: the batch's tokens, where the caller has counted them (layers of one batch)."""
         import torch
         for t, name in ((q, "q"), (k_cache, "k_cache"), (v_cache, "v_cache"), (page_table, "page_table")):
             if not t.is_cuda or not t.is_contiguous():
                 raise ValueError(f"{name} must be a contiguous device tensor")
         if page_table.dtype != torch.int32:
             raise TypeError("page_table must be int32")
-        if v_cache.shape != (k_cache.shape[0], k_cache.shape[1], k_cache.shape[3], k_cache.shape[2]):
+        ks = k_cache.shape
+        if v_cache.shape != (ks[0], ks[1], ks[3], ks[2]):
             raise ValueError("v_cache must be [P, h_kv, d, page_size] for k_cache [P, h_kv, page_size, d]")
-        n_tok = int(b.rows[:, 2].sum()) if len(b.rows) else 0
+        n_tok = b.num_tokens() if n_tok is None else n_tok
         if q.shape[0] != n_tok:
             raise ValueError(f"q has {q.shape[0]} rows, the batch schedules {n_tok} tokens")
         if page_table.dim() != 2 or page_table.shape[0] < len(b.rows):
@@ -409,22 +431,20 @@ class Context:
                          out=None, workspace=None, stream=None, num_layers: int = 1, check_errors: bool = False):
         """One layer (duet_attn_mixed_batch).  num_layers only sizes the workspace and the model."""
         import torch
-        shape = shape_of(q, k_cache, num_layers)
+        shape = _shape_c(shape_of(q, k_cache, num_layers))
         b = _BatchC(seq_meta)
         self._check_layer(q, k_cache, v_cache, page_table, b)
-        need = workspace_bytes(shape, b.rows)
-        ws = self.workspace(need) if workspace is None else workspace
+        ws = self.workspace(_workspace_bytes(shape, b)) if workspace is None else workspace  # the call checks its size
         if out is None:
             out = torch.empty_like(q)
-        st = torch.cuda.current_stream(q.device).cuda_stream if stream is None else stream
-        N.check(N.lib().duet_attn_mixed_batch(self.handle, ctypes.byref(_shape_c(shape)), q.data_ptr(),
+        st = _stream_of(q, stream)
+        N.check(N.lib().duet_attn_mixed_batch(self.handle, ctypes.byref(shape), q.data_ptr(),
                                               k_cache.data_ptr(), v_cache.data_ptr(), int(k_cache.shape[0]),
                                               page_table.data_ptr(), int(page_table.shape[1]), ctypes.byref(b.c),
-                                              cu_split.to_c(), ws.data_ptr(), ws.numel(), out.data_ptr(),
-                                              ctypes.c_void_p(st)), "duet_attn_mixed_batch")
+                                              cu_split.to_c(), ws.data_ptr(), ws.numel(), out.data_ptr(), st),
+                "duet_attn_mixed_batch")
         if check_errors:
-            N.check(N.lib().duet_check_device_error(self.handle, ws.data_ptr(), ctypes.c_void_p(st)),
-                    "duet_check_device_error")
+            N.check(N.lib().duet_check_device_error(self.handle, ws.data_ptr(), st), "duet_check_device_error")
         return out
 
     def attn_mixed_batch_noalloc(self, q, k_cache, v_cache, page_table, seq_meta, cu_split: CuSplit = CuSplit.agg(), *,
@@ -437,12 +457,12 @@ class Context:
         self._check_layer(q, k_cache, v_cache, page_table, b)
         if out is None:
             out = torch.empty_like(q)
-        st = torch.cuda.current_stream(q.device).cuda_stream if stream is None else stream
+        st = _stream_of(q, stream)
         N.check(N.lib().duet_attn_mixed_batch_noalloc(self.handle, ctypes.byref(_shape_c(shape)), q.data_ptr(),
                                                       k_cache.data_ptr(), v_cache.data_ptr(), int(k_cache.shape[0]),
                                                       page_table.data_ptr(), int(page_table.shape[1]),
                                                       ctypes.byref(b.c), cu_split.to_c(), out.data_ptr(),
-                                                      ctypes.c_void_p(st)), "duet_attn_mixed_batch_noalloc")
+                                                      st), "duet_attn_mixed_batch_noalloc")
         return out
 
     def block_forward(self, x, weights, k_caches, v_caches, page_table, seq_meta, ffn_dim: int,
@@ -458,7 +478,7 @@ class Context:
         if L < 1 or len(k_caches) != L or len(v_caches) != L:
             raise ValueError("weights, k_caches and v_caches must be non-empty lists of equal length")
         b = _BatchC(seq_meta)
-        n_tok = int(b.rows[:, 2].sum()) if len(b.rows) else 0
+        n_tok = b.num_tokens()
         kc0 = k_caches[0]
         shape = AttnShape(int(x.shape[1]) // int(kc0.shape[3]), int(kc0.shape[1]), int(kc0.shape[3]), "bf16",
                           int(kc0.shape[2]), L)
@@ -470,15 +490,16 @@ class Context:
         d_qkv = (shape.num_q_heads + 2 * shape.num_kv_heads) * dh
         want = {"attn_norm": (d,), "w_qkv": (d, d_qkv), "w_o": (d, d), "ffn_norm": (d,), "w_gate_up": (d, 2 * ffn_dim),
                 "w_down": (ffn_dim, d)}
+        xq = x.view(n_tok, shape.num_q_heads, dh)
         for l, w in enumerate(weights):
             for name in BLOCK_WEIGHT_NAMES:
                 t = w[name]
-                if tuple(t.shape) != want[name] or t.dtype != torch.bfloat16 or not t.is_cuda or not t.is_contiguous():
+                if t.shape != want[name] or t.dtype != torch.bfloat16 or not t.is_cuda or not t.is_contiguous():
                     raise ValueError(f"layer {l}: {name} must be a contiguous bf16 device tensor {want[name]}")
-            self._check_layer(x.view(n_tok, shape.num_q_heads, dh), k_caches[l], v_caches[l], page_table, b)
+            self._check_layer(xq, k_caches[l], v_caches[l], page_table, b, n_tok)
         block = BlockShape(int(ffn_dim), 0, BLOCK_GQA_QKV | BLOCK_FUSED_GATE_UP)
         k = int(cu_split.k_decode_steps)
-        n_dec = int((b.rows[:, 0] == KIND_DECODE).sum()) if len(b.rows) else 0
+        n_dec = b.num_decodes()
         xa = list(x_ahead or [])
         if k > 1 and n_dec > 0:
             if len(xa) != k - 1:
@@ -486,20 +507,19 @@ class Context:
             for t in xa:
                 if t.dtype != torch.bfloat16 or not t.is_cuda or not t.is_contiguous() or tuple(t.shape) != (n_dec, d):
                     raise ValueError(f"x_ahead tensors must be contiguous bf16 device tensors [{n_dec}, {d}]")
-        need = block_workspace_bytes(shape, block, b.rows, k)
-        ws = self.workspace(need) if workspace is None else workspace
+        ws = self.workspace(block_workspace_bytes(shape, block, b.rows, k)) if workspace is None else workspace
         wts = (N.BlockWeights * L)(*[N.BlockWeights(*[w[n].data_ptr() for n in BLOCK_WEIGHT_NAMES]) for w in weights])
         arr = lambda ts: (ctypes.c_void_p * L)(*[t.data_ptr() for t in ts])
-        st = torch.cuda.current_stream(x.device).cuda_stream if stream is None else stream
+        st = _stream_of(x, stream)
         N.check(N.lib().duet_block_forward(self.handle, ctypes.byref(_shape_c(shape)), ctypes.byref(block.to_c()), wts,
                                            float(norm_eps), x.data_ptr(),
                                            (ctypes.c_void_p * max(1, len(xa)))(*[t.data_ptr() for t in xa]) if xa else None,
                                            arr(k_caches), arr(v_caches),
                                            int(kc0.shape[0]), page_table.data_ptr(), int(page_table.shape[1]),
                                            ctypes.byref(b.c), cu_split.to_c(), ws.data_ptr(), ws.numel(),
-                                           ctypes.c_void_p(st)), "duet_block_forward")
+                                           st), "duet_block_forward")
         if check_errors:
-            N.check(N.lib().duet_check_device_error(self.handle, ws.data_ptr(), ctypes.c_void_p(st)),
+            N.check(N.lib().duet_check_device_error(self.handle, ws.data_ptr(), st),
                     "duet_check_device_error")
         return x
 
@@ -508,9 +528,9 @@ class Context:
         import torch
         if out is None:
             out = torch.empty_like(x)
-        st = torch.cuda.current_stream(x.device).cuda_stream if stream is None else stream
+        st = _stream_of(x, stream)
         N.check(N.lib().duet_rmsnorm(self.handle, x.data_ptr(), weight.data_ptr(), out.data_ptr(), int(x.shape[0]),
-                                     int(x.shape[1]), float(eps), ctypes.c_void_p(st)), "duet_rmsnorm")
+                                     int(x.shape[1]), float(eps), st), "duet_rmsnorm")
         return out
 
     def swiglu(self, gate_up, *, out=None, stream=None):
@@ -519,8 +539,8 @@ class Context:
         rows, m2 = int(gate_up.shape[0]), int(gate_up.shape[1])
         if out is None:
             out = torch.empty(rows, m2 // 2, dtype=gate_up.dtype, device=gate_up.device)
-        st = torch.cuda.current_stream(gate_up.device).cuda_stream if stream is None else stream
-        N.check(N.lib().duet_swiglu(self.handle, gate_up.data_ptr(), out.data_ptr(), rows, m2 // 2, ctypes.c_void_p(st)),
+        st = _stream_of(gate_up, stream)
+        N.check(N.lib().duet_swiglu(self.handle, gate_up.data_ptr(), out.data_ptr(), rows, m2 // 2, st),
                 "duet_swiglu")
         return out
 
@@ -533,13 +553,13 @@ class Context:
         if q is None:
             q = torch.empty(T, shape.num_q_heads, shape.head_dim, dtype=qkv.dtype, device=qkv.device)
         ws = self.workspace(workspace_bytes(shape, b.rows)) if workspace is None else workspace
-        st = torch.cuda.current_stream(qkv.device).cuda_stream if stream is None else stream
+        st = _stream_of(qkv, stream)
         N.check(N.lib().duet_qkv_split(self.handle, ctypes.byref(_shape_c(shape)), qkv.data_ptr(), q.data_ptr(),
                                        k_cache.data_ptr(), v_cache.data_ptr(), int(k_cache.shape[0]),
                                        page_table.data_ptr(), int(page_table.shape[1]), ctypes.byref(b.c),
-                                       ws.data_ptr(), ws.numel(), ctypes.c_void_p(st)), "duet_qkv_split")
+                                       ws.data_ptr(), ws.numel(), st), "duet_qkv_split")
         if check_errors:
-            N.check(N.lib().duet_check_device_error(self.handle, ws.data_ptr(), ctypes.c_void_p(st)),
+            N.check(N.lib().duet_check_device_error(self.handle, ws.data_ptr(), st),
                     "duet_check_device_error")
         return q
 
@@ -551,25 +571,25 @@ class Context:
         L = len(qs)
         if L < 1 or len(k_caches) != L or len(v_caches) != L or (outs is not None and len(outs) != L):
             raise ValueError("qs, k_caches, v_caches (and outs) must be non-empty lists of equal length")
-        shape = shape_of(qs[0], k_caches[0], L)
+        shape = _shape_c(shape_of(qs[0], k_caches[0], L))
         b = _BatchC(seq_meta)
+        n_tok = b.num_tokens()
         for l in range(L):
             if qs[l].shape != qs[0].shape or qs[l].dtype != qs[0].dtype or k_caches[l].shape != k_caches[0].shape:
                 raise ValueError(f"layer {l}: shapes differ from layer 0")
-            self._check_layer(qs[l], k_caches[l], v_caches[l], page_table, b)
-        need = workspace_bytes(shape, b.rows)
-        ws = self.workspace(need) if workspace is None else workspace
+            self._check_layer(qs[l], k_caches[l], v_caches[l], page_table, b, n_tok)
+        ws = self.workspace(_workspace_bytes(shape, b)) if workspace is None else workspace  # the call checks its size
         if outs is None:
             outs = [torch.empty_like(x) for x in qs]
         arr = lambda ts: (ctypes.c_void_p * L)(*[t.data_ptr() for t in ts])
-        st = torch.cuda.current_stream(qs[0].device).cuda_stream if stream is None else stream
-        N.check(N.lib().duet_attn_iteration(self.handle, ctypes.byref(_shape_c(shape)), arr(qs), arr(k_caches),
+        st = _stream_of(qs[0], stream)
+        N.check(N.lib().duet_attn_iteration(self.handle, ctypes.byref(shape), arr(qs), arr(k_caches),
                                             arr(v_caches), int(k_caches[0].shape[0]), page_table.data_ptr(),
                                             int(page_table.shape[1]), ctypes.byref(b.c), cu_split.to_c(),
-                                            ws.data_ptr(), ws.numel(), arr(outs), ctypes.c_void_p(st)),
+                                            ws.data_ptr(), ws.numel(), arr(outs), st),
                 "duet_attn_iteration")
         if check_errors:
-            N.check(N.lib().duet_check_device_error(self.handle, ws.data_ptr(), ctypes.c_void_p(st)),
+            N.check(N.lib().duet_check_device_error(self.handle, ws.data_ptr(), st),
                     "duet_check_device_error")
         return outs
 
@@ -592,20 +612,19 @@ class Context:
             raise ValueError(f"q_ahead, k_ahead and v_ahead need (k - 1) * L = {n_ahead} tensors")
         shape = shape_of(qs[0], k_caches[0], L)
         b = _BatchC(seq_meta)
-        n_dec = int((b.rows[:, 0] == 1).sum()) if len(b.rows) else 0
+        n_dec, n_tok, dtype = b.num_decodes(), b.num_tokens(), qs[0].dtype
         for l in range(L):
-            if qs[l].shape != qs[0].shape or qs[l].dtype != qs[0].dtype or k_caches[l].shape != k_caches[0].shape:
+            if qs[l].shape != qs[0].shape or qs[l].dtype != dtype or k_caches[l].shape != k_caches[0].shape:
                 raise ValueError(f"layer {l}: shapes differ from layer 0")
-            self._check_layer(qs[l], k_caches[l], v_caches[l], page_table, b)
-        for x in range(n_ahead):
-            for t, name, h in ((q_ahead[x], "q_ahead", shape.num_q_heads), (k_ahead[x], "k_ahead", shape.num_kv_heads),
-                               (v_ahead[x], "v_ahead", shape.num_kv_heads)):
-                if not t.is_cuda or not t.is_contiguous() or t.dtype != qs[0].dtype or \
-                        tuple(t.shape) != (n_dec, h, shape.head_dim):
-                    raise ValueError(f"{name}[{x}] must be a contiguous {qs[0].dtype} device tensor "
-                                     f"[{n_dec}, {h}, {shape.head_dim}]")
-        need = lookahead_workspace_bytes(shape, b.rows, k)
-        ws = self.workspace(need) if workspace is None else workspace
+            self._check_layer(qs[l], k_caches[l], v_caches[l], page_table, b, n_tok)
+        for ts, name, h in ((q_ahead, "q_ahead", shape.num_q_heads), (k_ahead, "k_ahead", shape.num_kv_heads),
+                            (v_ahead, "v_ahead", shape.num_kv_heads)):
+            want = (n_dec, h, shape.head_dim)
+            for x, t in enumerate(ts):
+                if not t.is_cuda or not t.is_contiguous() or t.dtype != dtype or t.shape != want:
+                    raise ValueError(f"{name}[{x}] must be a contiguous {dtype} device tensor [{n_dec}, {h}, "
+                                     f"{shape.head_dim}]")
+        ws = self.workspace(lookahead_workspace_bytes(shape, b.rows, k)) if workspace is None else workspace
         if outs is None:
             outs = [torch.empty_like(x) for x in qs]
         if outs_ahead is None:
@@ -613,15 +632,15 @@ class Context:
         if len(outs_ahead) != n_ahead:
             raise ValueError(f"outs_ahead needs {n_ahead} tensors")
         arr = lambda ts, n: (ctypes.c_void_p * max(n, 1))(*[t.data_ptr() for t in ts])
-        st = torch.cuda.current_stream(qs[0].device).cuda_stream if stream is None else stream
+        st = _stream_of(qs[0], stream)
         N.check(N.lib().duet_attn_lookahead(self.handle, ctypes.byref(_shape_c(shape)), arr(qs, L),
                                             arr(q_ahead, n_ahead), arr(k_ahead, n_ahead), arr(v_ahead, n_ahead),
                                             arr(k_caches, L), arr(v_caches, L), int(k_caches[0].shape[0]),
                                             page_table.data_ptr(), int(page_table.shape[1]), ctypes.byref(b.c),
                                             cu_split.to_c(), ws.data_ptr(), ws.numel(), arr(outs, L),
-                                            arr(outs_ahead, n_ahead), ctypes.c_void_p(st)), "duet_attn_lookahead")
+                                            arr(outs_ahead, n_ahead), st), "duet_attn_lookahead")
         if check_errors:
-            N.check(N.lib().duet_check_device_error(self.handle, ws.data_ptr(), ctypes.c_void_p(st)),
+            N.check(N.lib().duet_check_device_error(self.handle, ws.data_ptr(), st),
                     "duet_check_device_error")
         return outs, outs_ahead
 
@@ -639,10 +658,10 @@ class Context:
         if not 0 <= req < page_table.shape[0]:
             raise ValueError(f"request {req} outside the page table's {page_table.shape[0]} rows")
         out = torch.empty(kv_len, shape.num_kv_heads, shape.head_dim, dtype=cache.dtype, device=cache.device)
-        st = torch.cuda.current_stream(cache.device).cuda_stream
+        st = _stream_of(cache, None)
         N.check(N.lib().duet_gather_kv(self.handle, ctypes.byref(_shape_c(shape)), which, cache.data_ptr(),
                                        int(cache.shape[0]), page_table.data_ptr(), int(page_table.shape[1]), req,
-                                       kv_len, out.data_ptr(), ctypes.c_void_p(st)), "duet_gather_kv")
+                                       kv_len, out.data_ptr(), st), "duet_gather_kv")
         return out
 
     def set_profiling(self, level):

@@ -490,7 +490,10 @@ int duet_lookahead_workspace_bytes(const duet_shape* shape, const duet_batch* ba
  *   q_ahead, k_ahead, v_ahead and out_ahead are host arrays of (k - 1) * num_layers device
  *   pointers to [R_d, h_q or h_kv, d] tensors (R_d = number of decode requests), caller-owned;
  *   they may be NULL when k == 1 or R_d == 0.
- * Steps run in order, so step s reads the tokens steps 1 .. s - 1 wrote.  Every decode request's
+ * Steps run in order, so step s reads the tokens steps 1 .. s - 1 wrote.  When no input shares memory
+ * with an output or a cache and no two caches share memory, one kernel writes the tokens of every
+ * step ahead of step 0 (a step reads none past its own) and a layer's output may be completed by
+ * the step's next layer; otherwise each layer of each step is on its own.  Every decode request's
  * page_table row must hold pages for cached_len + k tokens; the slots written must not be read
  * by any other request of the batch (the prefill half runs at the same time).
  * SPLIT / CONCURRENT: the first prefill layer is enqueued on the prefill stream, then every decode

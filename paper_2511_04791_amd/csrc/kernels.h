@@ -71,16 +71,21 @@ struct WorkArgs {
   long long prefill_tiles;      // key tiles over all units (bf16)
 };
 
-// One decode step's cache write (look-ahead decode): new key and value rows in, paged cache out.
-struct AppendArgs {
+// Cache writes of look-ahead decode steps: new key and value rows in, paged cache out.  Job x writes step
+// x / layers + 1 of layer x % layers.
+struct AppendJob {
+  const void* k_new;     // [R_d, h_kv, d], decode requests in order
+  const void* v_new;     // [R_d, h_kv, d]
   void* k_cache;         // [P, h_kv, 16, d], written
   void* v_cache;         // [P, h_kv, d, 16], written
-  const void* k_new;     // [R_d, h_kv, d]: row = the request's q_start in the step's metadata
-  const void* v_new;     // [R_d, h_kv, d]
+};
+struct AppendArgs {
+  const AppendJob* jobs;
   const int32_t* page_table;
   long long num_phys_pages;
   int32_t max_pages;
   int32_t h_kv, head_dim, dtype;
+  int32_t first_job, n_jobs, layers;  // jobs first_job .. first_job + n_jobs - 1
 };
 
 // Decode split length in pages.
@@ -245,7 +250,7 @@ hipError_t launch_mixed(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
 // The fp32 paths of the two launchers above.
 hipError_t launch_decode_partial_f32(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
 hipError_t launch_prefill_f32(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
-// Writes the new token of every decode request in w.dreq (position = meta cached_len).
+// Writes the new tokens of every decode request in w.dreq (step 0's lists) for the launch's jobs.
 hipError_t launch_kv_append(const AppendArgs& a, const WorkArgs& w, hipStream_t s);
 
 hipError_t launch_gather(const void* cache, int which, int elem_bytes, int h_kv, int d, const int32_t* page_table,

@@ -99,13 +99,14 @@ struct Plan {
   std::vector<PrefillUnit> punits;
   std::vector<int4> ditems;
   std::vector<StepPlan> ahead;  // look-ahead decode steps 1 .. steps - 1
+  std::vector<AppendJob> append;  // cache writes of those steps, filled by the caller of plan_batch
   int steps = 1;
   int n_items_decode = 0, max_split = 0, group = 0, prefill_id_cap = 0;
   DecodeRule decode{};
   int n_punits = 0, n_slots = 0;
   int64_t prefill_tiles = 0;
-  size_t off_meta = 0, off_pitems = 0, off_dreq = 0, off_ditems = 0, off_punits = 0, off_pcount = 0, off_ppart = 0,
-         upload_bytes = 0, total = 0;
+  size_t off_meta = 0, off_pitems = 0, off_dreq = 0, off_ditems = 0, off_punits = 0, off_pcount = 0, off_append = 0,
+         off_ppart = 0, upload_bytes = 0, total = 0;
   // Two buffers of split-K partials: consecutive layers of a call alternate between them, so a
   // layer's partials survive until the next layer's decode kernel has merged them.
   size_t off_pacc[2] = {0, 0}, off_pml[2] = {0, 0};
@@ -335,6 +336,9 @@ void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps,
     sp.off_ditems = off;
     off = align_up(off + (s->dtype == DUET_BF16 ? (size_t)ni * sizeof(int4) : 0));
   }
+  p->append.clear();
+  p->off_append = off;
+  if (n_dreq > 0) off = align_up(off + (size_t)(steps - 1) * layers * sizeof(AppendJob));
   p->upload_bytes = off;
   for (int b = 0; b < 2; ++b) {
     p->off_pacc[b] = off;
@@ -401,8 +405,8 @@ void append_key(std::vector<uint64_t>* k, const DecodeLaunch& l) {
                         bits(w.merge_out), bits(w.n_merge), bits(w.n_pitems), bits(w.n_dreq), bits(w.max_split),
                         bits(w.n_ditems), bits(w.decode_small), bits(w.decode_pps), bits(w.decode_cus), bits(w.prefill_id_cap),
                         bits(w.ppart), bits(w.punits), bits(w.n_punits), bits(w.pcount), bits(w.prefill_tiles),
-                        bits(p.k_cache), bits(p.v_cache), bits(p.k_new), bits(p.v_new), bits(p.page_table),
-                        bits(p.num_phys_pages), bits(p.max_pages), bits(p.h_kv), bits(p.head_dim), bits(p.dtype)};
+                        bits(p.jobs), bits(p.page_table), bits(p.num_phys_pages), bits(p.max_pages), bits(p.h_kv),
+                        bits(p.head_dim), bits(p.dtype), bits(p.first_job), bits(p.n_jobs), bits(p.layers)};
   k->insert(k->end(), std::begin(f), std::end(f));
 }
 
@@ -568,6 +572,7 @@ int stage_upload(duet_ctx* ctx, const Plan& p, char* ws, hipStream_t st, bool ma
   std::memcpy(h + p.off_ditems, p.ditems.data(), p.ditems.size() * sizeof(int4));
   std::memcpy(h + p.off_punits, p.punits.data(), p.punits.size() * sizeof(PrefillUnit));
   std::memset(h + p.off_pcount, 0, (size_t)p.n_slots * sizeof(int32_t));
+  std::memcpy(h + p.off_append, p.append.data(), p.append.size() * sizeof(AppendJob));
   for (const StepPlan& sp : p.ahead) {
     std::memcpy(h + sp.off_meta, sp.meta.data(), sp.meta.size() * sizeof(int4));
     std::memcpy(h + sp.off_dreq, sp.dreq.data(), sp.dreq.size() * sizeof(int4));
@@ -770,8 +775,8 @@ int attn_layers(duet_ctx* ctx, const duet_shape* shape, int layers, const void* 
   }
   // bf16 decode defers each layer's split merge into the next layer's partial kernel, whose waves
   // merge once their item queue is empty; partial buffers and counter sets alternate by layer,
-  // and one reduce kernel merges the last layer.  The fp32 path merges every layer in its own
-  // reduce kernel; a small bf16 batch merges inside its one decode kernel.
+  // and one reduce kernel merges the last layer.  The fp32 path and a small bf16 batch merge every
+  // layer in its own reduce kernel.
   const bool defer = has_decode && shape->dtype == DUET_BF16 && !w.decode_small;
   // Aggregated, a layer's two halves are one launch (attn_mixed.hip); per-kernel profiling keeps them
   // apart.
@@ -894,8 +899,56 @@ int run_decode_step(duet_ctx* ctx, const std::vector<DecodeLaunch>& launches, hi
   return DUET_OK;
 }
 
+// Whether the cache writes of every look-ahead step may go ahead of the steps and a layer's merge into the
+// next layer's kernel: no two caches of the call share memory (a later layer would write over the rows an earlier one reads), and no query, key or value
+// tensor shares any with an output or a cache (such a row may be there only once the step before has run).
+bool steps_independent(const duet_shape* s, const duet_batch* b, int n_dec, int layers, int k, int64_t num_phys_pages,
+                     const void* const* q_l, const void* const* q_ahead, const void* const* k_ahead,
+                     const void* const* v_ahead, void* const* kc_l, void* const* vc_l, void* const* out_l,
+                     void* const* out_ahead) {
+  const int n = (k - 1) * layers;
+  const size_t row = (size_t)s->head_dim * (s->dtype == DUET_BF16 ? 2 : 4);
+  const size_t cache = (size_t)num_phys_pages * s->num_kv_heads * s->page_size * row;
+  size_t tokens = 0;
+  for (int r = 0; r < b->num_reqs; ++r) tokens += b->reqs[r].q_len;
+  typedef std::pair<uintptr_t, uintptr_t> Range;
+  auto range = [](const void* p, size_t bytes) {
+    return Range(reinterpret_cast<uintptr_t>(p), reinterpret_cast<uintptr_t>(p) + bytes);
+  };
+  std::vector<Range> out;
+  out.reserve(3 * layers + n);
+  for (int l = 0; l < layers; ++l) {
+    out.push_back(range(kc_l[l], cache));
+    out.push_back(range(vc_l[l], cache));
+  }
+  std::sort(out.begin(), out.end());
+  for (size_t i = 1; i < out.size(); ++i)
+    if (out[i - 1].second > out[i].first) return false;
+  for (int l = 0; l < layers; ++l) out.push_back(range(out_l[l], tokens * s->num_q_heads * row));
+  for (int x = 0; x < n; ++x) out.push_back(range(out_ahead[x], (size_t)n_dec * s->num_q_heads * row));
+  std::sort(out.begin(), out.end());
+  // out[i].second becomes the furthest end of the first i + 1 ranges: outputs may lie in one another.
+  for (size_t i = 1; i < out.size(); ++i) out[i].second = std::max(out[i].second, out[i - 1].second);
+  size_t at = 0;  // ranges that start before the last input's end; tensors often lie in order
+  auto free_of = [&](const void* p, size_t bytes) {
+    const Range in = range(p, bytes);
+    if ((at > 0 && out[at - 1].first >= in.second) || (at < out.size() && out[at].first < in.second))
+      at = std::lower_bound(out.begin(), out.end(), Range(in.second, 0)) - out.begin();
+    return at == 0 || out[at - 1].second <= in.first;
+  };
+  for (int l = 0; l < layers; ++l)
+    if (!free_of(q_l[l], tokens * s->num_q_heads * row)) return false;
+  for (int x = 0; x < n; ++x) {
+    if (!free_of(q_ahead[x], (size_t)n_dec * s->num_q_heads * row)) return false;
+    if (!free_of(k_ahead[x], (size_t)n_dec * s->num_kv_heads * row)) return false;
+    if (!free_of(v_ahead[x], (size_t)n_dec * s->num_kv_heads * row)) return false;
+  }
+  return true;
+}
+
 // Look-ahead decode (Section 4.3): the prefill half once over all layers and the decode half for
-// k = split.k_decode_steps steps, step s >= 1 writing its token before attending.  SPLIT and
+// k = split.k_decode_steps steps, step s >= 1 attending its token too; the tokens of every step are written
+// ahead of step 0, or, where steps_independent says no, each before its layer's attention.  SPLIT and
 // CONCURRENT enqueue the first prefill layer, every decode step (one graph) on the decode stream,
 // then the other prefill layers; AGG runs decode step 0, the prefill layers and decode steps
 // 1 .. k - 1 in that order on the caller's stream.
@@ -957,6 +1010,11 @@ int attn_lookahead(duet_ctx* ctx, const duet_shape* shape, const void* const* q_
   const bool prof = ctx->profiling >= 2;
   const bool has_decode = n_dec > 0, has_prefill = w.n_pitems > 0;
   if (prof_iter && ((rc = ensure_step_events(ctx, k)) || (rc = ensure_layer_events(ctx, layers)))) return rc;
+  if (has_decode)
+    for (int x = 0; x < (k - 1) * layers; ++x)
+      p.append.push_back({k_ahead[x], v_ahead[x], kc_l[x % layers], vc_l[x % layers]});
+  const bool independent = has_decode && steps_independent(shape, batch, n_dec, layers, k, num_phys_pages, q_l, q_ahead,
+                                                           k_ahead, v_ahead, kc_l, vc_l, out_l, out_ahead);
 
   if (prof_iter) HIP_TRY(hipEventRecord(ctx->prof[kEvFork], order));
   if ((rc = stage_upload(ctx, p, ws, order))) return rc;
@@ -966,6 +1024,16 @@ int attn_lookahead(duet_ctx* ctx, const duet_shape* shape, const void* const* q_
     if (has_prefill) HIP_TRY(hipStreamWaitEvent(sp, ctx->ev_fork, 0));
   }
   std::vector<DecodeLaunch> launches;
+  AppendArgs append{};
+  append.jobs = reinterpret_cast<const AppendJob*>(ws + p.off_append);
+  append.page_table = page_table;
+  append.num_phys_pages = num_phys_pages;
+  append.max_pages = max_pages_per_req;
+  append.h_kv = shape->num_kv_heads;
+  append.head_dim = shape->head_dim;
+  append.dtype = shape->dtype;
+  append.n_jobs = (int)p.append.size();
+  append.layers = layers;
   // Appends decode step st's launches (every layer) to `launches`.
   auto add_step = [&](int st) {
     WorkArgs ws_w = w;
@@ -990,22 +1058,35 @@ int attn_lookahead(duet_ctx* ctx, const duet_shape* shape, const void* const* q_
       dl.a.out = st == 0 ? out_l[l] : out_ahead[x];
       dl.w = ws_w;
       dl.ap = AppendArgs{};
-      if (st > 0) {
-        dl.ap.k_cache = kc_l[l];
-        dl.ap.v_cache = vc_l[l];
-        dl.ap.k_new = k_ahead[x];
-        dl.ap.v_new = v_ahead[x];
-        dl.ap.page_table = page_table;
-        dl.ap.num_phys_pages = num_phys_pages;
-        dl.ap.max_pages = max_pages_per_req;
-        dl.ap.h_kv = shape->num_kv_heads;
-        dl.ap.head_dim = shape->head_dim;
-        dl.ap.dtype = shape->dtype;
+      if (st > 0 && !independent) {
+        dl.ap = append;
+        dl.ap.first_job = x;
+        dl.ap.n_jobs = 1;
+        dl.w = w;
         dl.kind = DecodeLaunch::kAppend;
         launches.push_back(dl);
+        dl.ap = AppendArgs{};
+        dl.w = ws_w;
+      }
+      // bf16 merges are deferred as in attn_layers, within the step: the next step's splits differ (8 steps,
+      // 2 layers, 16 requests of 512 to 4096 tokens, 32 / 8 heads of 128: 512 us without, 489 with).
+      const bool defer = independent && shape->dtype == DUET_BF16 && !dl.w.decode_small;
+      if (defer) {
+        const int cur = l & 1, prev = cur ^ 1;
+        dl.w.pacc = reinterpret_cast<float*>(ws + p.off_pacc[cur]);
+        dl.w.pml = reinterpret_cast<float*>(ws + p.off_pml[cur]);
+        dl.w.work_counter = w.work_counter + cur * kDecodeSetInts;
+        dl.w.clear_counter = w.work_counter + prev * kDecodeSetInts;
+        if (l > 0) {
+          dl.w.merge_pacc = reinterpret_cast<const float*>(ws + p.off_pacc[prev]);
+          dl.w.merge_pml = reinterpret_cast<const float*>(ws + p.off_pml[prev]);
+          dl.w.merge_out = st == 0 ? out_l[l - 1] : out_ahead[x - 1];
+          dl.w.n_merge = w.n_dreq * a.h_q;
+        }
       }
       dl.kind = DecodeLaunch::kPartial;
       launches.push_back(dl);
+      if (defer && l < layers - 1) continue;
       dl.kind = DecodeLaunch::kReduce;
       launches.push_back(dl);
     }
@@ -1019,6 +1100,14 @@ int attn_lookahead(duet_ctx* ctx, const duet_shape* shape, const void* const* q_
     for (int st = first; st < last;) {
       const int end = prof_iter && st == 0 ? 1 : last;
       launches.clear();
+      if (st == 0 && independent && append.n_jobs > 0) {
+        DecodeLaunch dl;
+        dl.kind = DecodeLaunch::kAppend;
+        dl.a = a;
+        dl.w = w;
+        dl.ap = append;
+        launches.push_back(dl);
+      }
       for (int x = st; x < end; ++x) add_step(x);
       int r2 = run_decode_step(ctx, launches, ds);
       if (r2) return r2;

@@ -31,7 +31,6 @@ measured beside the model's prediction.
 from __future__ import annotations
 
 import argparse
-import hashlib
 import json
 import math
 import os
@@ -72,11 +71,6 @@ def prefill_causal_flops(batch) -> float:
     return tot
 
 
-def source_hash(name: str) -> str:
-    with open(os.path.join(ROOT, "paper_2511_04791_amd", "csrc", name), "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
-
-
 def split_tag(split) -> str:
     """Name of a CU split in profile file names: 'agg' or 'S_p-S_d'."""
     from paper_2511_04791_amd import SPLIT
@@ -86,6 +80,7 @@ def split_tag(split) -> str:
 def committed_traffic(kernel: str, source: str, tag: str):
     """HBM bytes per launch from the committed counter summary of `kernel` on `tag` (workload and
     CU split), if the kernel source still matches the one the counters were taken on; else None."""
+    from paper_2511_04791_amd.profsum import source_hash
     path = os.path.join(ROOT, "profiles", f"{kernel}_{tag}_traffic.json")
     try:
         with open(path) as f:

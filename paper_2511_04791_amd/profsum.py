@@ -11,7 +11,7 @@
 counter runs (FETCH_SIZE, then WRITE_SIZE, in KiB per dispatch), scales each counter by what it
 reads for the plain 1 GiB device copy of the same run (a copy reads 1 GiB and writes 1 GiB), and
 writes, per attention kernel, `<kernel>_<tag>_traffic.json` (HBM bytes per launch, tagged with
-the hash of the kernel's source file) and `<kernel>_<tag>_traffic.md`.  `counters` prints, per
+the hash of the kernel's source) and `<kernel>_<tag>_traffic.md`.  `counters` prints, per
 attention kernel, the median per-dispatch value of every counter in the given runs and, where
 their counters are present, the MFMA busy fraction (SQ_VALU_MFMA_BUSY_CYCLES, summed over SIMDs,
 over the dispatch's GPU cycles -- GRBM_GUI_ACTIVE of one XCD -- times the chip's 1024 SIMDs), the MFMA work executed (SQ_INSTS_VALU_MFMA_MOPS_BF16,
@@ -24,6 +24,7 @@ import csv
 import hashlib
 import json
 import os
+import re
 import statistics
 import sys
 
@@ -34,6 +35,7 @@ KERNELS = {
     "decode_partial": ("decode_partial_bf16", "attn_decode.hip"),
     "decode_reduce": ("decode_reduce", "attn_decode.hip"),
     "prefill": ("prefill_bf16", "attn_prefill.hip"),
+    "mixed": ("mixed_bf16", "attn_mixed.hip"),  # both halves of an aggregated layer
 }
 COPY_BYTES = 1 << 30
 SIMDS = 1024  # 256 CUs x 4
@@ -41,8 +43,14 @@ XCDS = 8      # rocprofv3 sums GRBM_GUI_ACTIVE over the XCDs, which share one cl
 
 
 def source_hash(name: str) -> str:
+    """Hash of a kernel's source file and of the headers with device code that it includes."""
     with open(os.path.join(PKG, "csrc", name), "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+        text = f.read()
+    h = hashlib.sha256(text)
+    for header in re.findall(rb'#include "(\w+_device\.h)"', text):
+        with open(os.path.join(PKG, "csrc", header.decode()), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def warm_durations(trace_path: str, skip: int = 2) -> dict:

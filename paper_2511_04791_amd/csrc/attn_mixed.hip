@@ -45,7 +45,7 @@ __global__ __launch_bounds__(prefill::kThreads, 2) void mixed_bf16(AttnArgs a, W
   extern __shared__ __attribute__((aligned(16))) __bf16 lds[];
   const int b = blockIdx.x;
   if (b >= decode_blocks && b < decode_blocks + w.n_pitems) {
-    prefill::prefill_unit<D, NH>(a, w, b - decode_blocks, lds);
+    prefill::prefill_unit<D, NH, false>(a, w, b - decode_blocks, lds);
     return;
   }
   float* const fl = reinterpret_cast<float*>(lds);

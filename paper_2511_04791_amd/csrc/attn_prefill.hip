@@ -41,10 +41,28 @@ namespace {
 
 using namespace prefill;
 
-template <int D, int NH>
-__global__ __launch_bounds__(kThreads, 1) void prefill_bf16(AttnArgs a, WorkArgs w) {
+template <int D, int NH, bool kLean>
+__global__ __launch_bounds__(kThreads, kLean ? 4 : 1) void prefill_bf16(AttnArgs a, WorkArgs w) {
   extern __shared__ __attribute__((aligned(16))) __bf16 lds[];
-  prefill_unit<D, NH>(a, w, blockIdx.x, lds);
+  prefill_unit<D, NH, kLean>(a, w, blockIdx.x, lds);
+}
+
+// Heads of 64 hold half the ring and half the state of heads of 128, and their step is bound by the
+// softmax's vector instructions and its dependency stalls, not by the matrix cores: two lean workgroups
+// on a CU fill each other's stalls.  A lone lean workgroup is slower than a wide one, and with barely two
+// items per CU all start at once, so that nothing evens out a CU that got two long ones.  Hence lean
+// where every CU of the share gets two items and its mean load is at least 5/4 of the longest one.  Us a
+// layer, wide against lean (16 / 2 heads):
+//   512 items, load 1.5 / 2.0 / 3.0 times the longest (8192 tokens after 8192, 256 / 192 / 128 CUs)
+//     524 / 698 / 1005 against 468 / 539 / 790;
+//   280 items, load 1.27 (2048 tokens, 128 CUs) 49.7 against 43.3; on 192 and 256 CUs 40.6 and 31.3
+//     against 38.1 and 31.5, but 292 items (2048 after 2048) on 256 CUs 59.7 against 64.8;
+//   1280 items, load 1.0 (8192 tokens, 256 CUs) 184 against 197.
+template <int D>
+bool use_lean(const WorkArgs& w) {
+  return D == 64 && w.n_pitems >= 2 * w.prefill_cus &&
+         4 * w.prefill_tiles >= 5LL * w.prefill_longest * w.prefill_cus &&
+         2 * PrefillSmem<D>::bytes(w.prefill_id_cap) <= kLdsBytes;
 }
 
 // Merges the pieces of every unit of more than kPrefillSelfMerge: one wave per (unit, wave of the unit,
@@ -121,16 +139,19 @@ hipError_t launch_merge_nh(const AttnArgs& a, const WorkArgs& w, hipStream_t s) 
   }
 }
 
-template <int D, int NH>
+template <int D, int NH, bool kLean>
 hipError_t launch_bf16(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
+  if constexpr (D == 64 && !kLean) {
+    if (use_lean<D>(w)) return launch_bf16<D, NH, true>(a, w, s);
+  }
   static bool attr_set = false;  // the attribute is per function and process
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill_bf16<D, NH>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&prefill_bf16<D, NH, kLean>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)PrefillSmem<D>::kMaxBytes);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  hipLaunchKernelGGL((prefill_bf16<D, NH>), dim3(w.n_pitems), dim3(kThreads), PrefillSmem<D>::bytes(w.prefill_id_cap),
+  hipLaunchKernelGGL((prefill_bf16<D, NH, kLean>), dim3(w.n_pitems), dim3(kThreads), PrefillSmem<D>::bytes(w.prefill_id_cap),
                      s, a, w);
   return hipGetLastError();
 }
@@ -138,10 +159,10 @@ hipError_t launch_bf16(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
 template <int D>
 hipError_t launch_bf16_nh(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
   switch (prefill_heads_per_unit(a.group)) {
-    case 1: return launch_bf16<D, 1>(a, w, s);
-    case 2: return launch_bf16<D, 2>(a, w, s);
-    case 4: return launch_bf16<D, 4>(a, w, s);
-    default: return launch_bf16<D, 8>(a, w, s);
+    case 1: return launch_bf16<D, 1, false>(a, w, s);
+    case 2: return launch_bf16<D, 2, false>(a, w, s);
+    case 4: return launch_bf16<D, 4, false>(a, w, s);
+    default: return launch_bf16<D, 8, false>(a, w, s);
   }
 }
 

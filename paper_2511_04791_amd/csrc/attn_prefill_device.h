@@ -18,6 +18,7 @@ constexpr int kThreads = 64 * kWaves;
 // LDS ring of kStages tiles: the tile in use plus kStages - 1 in flight.
 constexpr int kStages = 4;
 static_assert(kStages >= 2, "the ring needs a tile in use and one in flight");
+constexpr size_t kLdsBytes = 160 * 1024;  // of a CU
 constexpr float kRescaleSlack = 8.0f;  // base-2 units: probabilities stay below 2^8
 
 // Direct global-to-LDS load of 16 bytes per lane: lane i of the wave writes lds_block + 16 i.
@@ -72,7 +73,11 @@ template <int D>
 constexpr size_t kSlotPairs = (size_t)kThreads * (D / 4 + 1);
 
 // Work item `index` of the list, by one workgroup of kThreads threads; lds: PrefillSmem bytes.
-template <int D, int NH>
+//
+// kLean keeps a wave within 128 registers, so that four of them share a SIMD: key fragments are read one
+// half of the tile at a time, value fragments after the softmax, and a merging piece reads its own
+// state back.  Every result is the same to the bit.
+template <int D, int NH, bool kLean>
 __device__ __forceinline__ void prefill_unit(const AttnArgs& a, const WorkArgs& w, int index, __bf16* const lds) {
   constexpr int BN = kPrefillKeys;       // keys per stage
   constexpr int KCH = D / 8;             // 16-byte chunks per K row
@@ -80,7 +85,6 @@ __device__ __forceinline__ void prefill_unit(const AttnArgs& a, const WorkArgs& 
   constexpr int NK = D / 16;             // MFMA k-steps over the head dim
   constexpr int NO = D / 32;             // 32-dim output tiles
   constexpr int WPH = kWaves / NH;       // waves per head
-  constexpr int QB = 32 * WPH;           // queries per unit
 
   const int tid = threadIdx.x;
   const int wave = uniform(tid >> 6);
@@ -250,10 +254,11 @@ __device__ __forceinline__ void prefill_unit(const AttnArgs& a, const WorkArgs& 
   // S^T of key tile kt for this wave's 32 rows: K fragments from LDS, Q^T from registers.
   auto scores = [&](int kt, f32x16 (&sacc)[2]) {
     const __bf16* ks = lds + (kt % kStages) * PrefillSmem<D>::kStageElems;
-    // All K fragments of the step are read before the first MFMA, so LDS latency is paid once.
+    // All K fragments of the step are read before the first MFMA, so LDS latency is paid once (lean:
+    // of each half of the keys).
     bf16x8 kf[2][NK];
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
+    for (int nb = 0; nb < (kLean ? 1 : 2); ++nb) {
       const int row = 32 * nb + swap_bits23(lane & 31);
 #pragma unroll
       for (int kk = 0; kk < NK; ++kk) {
@@ -273,8 +278,20 @@ __device__ __forceinline__ void prefill_unit(const AttnArgs& a, const WorkArgs& 
 #pragma unroll
     for (int kk = 0; kk < NK; ++kk)
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
+      for (int nb = 0; nb < (kLean ? 1 : 2); ++nb)
         sacc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[nb][kk], qf[kk], sacc[nb], 0, 0, 0);
+    if constexpr (kLean) {
+      __builtin_amdgcn_sched_barrier(0);
+      const int row = 32 + swap_bits23(lane & 31);
+#pragma unroll
+      for (int kk = 0; kk < NK; ++kk) {
+        const int ch = (2 * kk + hh) ^ (kswz(row) & (KCH - 1));
+        kf[1][kk] = *reinterpret_cast<const bf16x8*>(ks + row * D + ch * 8);
+      }
+#pragma unroll
+      for (int kk = 0; kk < NK; ++kk)
+        sacc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1][kk], qf[kk], sacc[1], 0, 0, 0);
+    }
   };
 
   for (int kt = kt0; kt < kt1; ++kt) {
@@ -286,10 +303,11 @@ __device__ __forceinline__ void prefill_unit(const AttnArgs& a, const WorkArgs& 
       f32x16 sacc[2];
       scores(kt, sacc);
       const __bf16* vs = lds + (kt % kStages) * PrefillSmem<D>::kStageElems + BN * D;
-      // V fragments are read now; their LDS latency hides behind the softmax below.
+      // V fragments are read now; their LDS latency hides behind the softmax below (lean: after it,
+      // behind the SIMD's other waves).
       bf16x8 vf[NO][4];
 #pragma unroll
-      for (int n = 0; n < NO; ++n) {
+      for (int n = 0; n < (kLean ? 0 : NO); ++n) {
         const int vrow = 32 * n + (lane & 31);
 #pragma unroll
         for (int k2 = 0; k2 < 4; ++k2) {
@@ -327,6 +345,7 @@ __device__ __forceinline__ void prefill_unit(const AttnArgs& a, const WorkArgs& 
         for (int n = 0; n < NO; ++n) oacc[n] *= alpha;
       }
       bf16x8 pb[4];
+      if constexpr (kLean) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
@@ -341,6 +360,18 @@ __device__ __forceinline__ void prefill_unit(const AttnArgs& a, const WorkArgs& 
           const bf16x2 two = {pb[k2][2 * e], pb[k2][2 * e + 1]};
           l_run = __builtin_amdgcn_fdot2_f32_bf16(two, ones, l_run, false);
         }
+      if constexpr (kLean) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int n = 0; n < NO; ++n) {
+          const int vrow = 32 * n + (lane & 31);
+#pragma unroll
+          for (int k2 = 0; k2 < 4; ++k2) {
+            const int ch = (2 * k2 + hh) ^ (vswz(vrow) & (VCH - 1));
+            vf[n][k2] = *reinterpret_cast<const bf16x8*>(vs + vrow * BN + ch * 8);
+          }
+        }
+      }
 #pragma unroll
       for (int n = 0; n < NO; ++n)
 #pragma unroll
@@ -405,16 +436,16 @@ __device__ __forceinline__ void prefill_unit(const AttnArgs& a, const WorkArgs& 
     }
     __syncthreads();
     if (!ids[0]) return;
-    // The last piece: combine the states in piece order (its own from registers, the others from
-    // their slots), so the result does not depend on which piece finished last.
+    // The last piece: combine the states in piece order (its own from registers, unless lean, the
+    // others from their slots), so the result does not depend on which piece finished last.
     f32x16 own[NO];
 #pragma unroll
-    for (int n = 0; n < NO; ++n) own[n] = oacc[n];
+    for (int n = 0; n < (kLean ? 0 : NO); ++n) own[n] = oacc[n];
     const u64 own_ml = pack(m_ref, l_run);
     for (int pc = 0; pc < n_pieces; ++pc) {
       f32x16 op[NO];
       u64 ml;
-      if (pc == piece) {
+      if (!kLean && pc == piece) {
         ml = own_ml;
 #pragma unroll
         for (int n = 0; n < NO; ++n) op[n] = own[n];

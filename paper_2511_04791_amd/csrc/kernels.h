@@ -62,6 +62,7 @@ struct WorkArgs {
   int32_t decode_pps;     // pages per bf16 decode item
   int32_t decode_small;   // bf16 decode items run one workgroup each and merge themselves (decode_rule)
   int32_t decode_cus;   // CUs the decode stream may use (sizes the persistent grid)
+  int32_t prefill_cus;  // CUs the prefill stream may use
   int32_t prefill_id_cap;  // most pages of any prefill request (sizes the LDS page-id table)
   // Prefill key split (bf16, see kPrefillPieceFill).
   float* ppart;               // [slots] partial state of every piece: unnormalised O, running max, denominator
@@ -69,6 +70,7 @@ struct WorkArgs {
   const PrefillUnit* punits;  // [n_punits] units for the merge kernel
   int32_t n_punits;
   long long prefill_tiles;      // key tiles over all units (bf16)
+  int32_t prefill_longest;      // key tiles of the longest item (bf16)
 };
 
 // Cache writes of look-ahead decode steps: new key and value rows in, paged cache out.  Job x writes step

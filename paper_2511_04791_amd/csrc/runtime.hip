@@ -403,8 +403,8 @@ void append_key(std::vector<uint64_t>* k, const DecodeLaunch& l) {
                         bits(w.pitems), bits(w.dreq), bits(w.pacc), bits(w.pml), bits(w.ditems), bits(w.err),
                         bits(w.work_counter), bits(w.clear_counter), bits(w.merge_pacc), bits(w.merge_pml),
                         bits(w.merge_out), bits(w.n_merge), bits(w.n_pitems), bits(w.n_dreq), bits(w.max_split),
-                        bits(w.n_ditems), bits(w.decode_small), bits(w.decode_pps), bits(w.decode_cus), bits(w.prefill_id_cap),
-                        bits(w.ppart), bits(w.punits), bits(w.n_punits), bits(w.pcount), bits(w.prefill_tiles),
+                        bits(w.n_ditems), bits(w.decode_small), bits(w.decode_pps), bits(w.decode_cus), bits(w.prefill_cus), bits(w.prefill_id_cap),
+                        bits(w.ppart), bits(w.punits), bits(w.n_punits), bits(w.pcount), bits(w.prefill_tiles), bits(w.prefill_longest),
                         bits(p.jobs), bits(p.page_table), bits(p.num_phys_pages), bits(p.max_pages), bits(p.h_kv),
                         bits(p.head_dim), bits(p.dtype), bits(p.first_job), bits(p.n_jobs), bits(p.layers)};
   k->insert(k->end(), std::begin(f), std::end(f));
@@ -688,6 +688,7 @@ void base_args(const duet_ctx* ctx, const duet_shape* shape, const Plan& p, char
   w->decode_small = p.decode.small;
   w->decode_pps = p.decode.pages_per_split;
   w->decode_cus = split.mode == DUET_SPLIT ? split.cus_decode : ctx->num_cus;
+  w->prefill_cus = split.mode == DUET_SPLIT ? split.cus_prefill : ctx->num_cus;
   w->n_pitems = (int)p.pitems.size();
   w->n_dreq = (int)p.dreq.size();
   w->max_split = p.max_split;
@@ -697,6 +698,7 @@ void base_args(const duet_ctx* ctx, const duet_shape* shape, const Plan& p, char
   w->n_punits = p.n_punits;
   w->pcount = reinterpret_cast<int32_t*>(ws + p.off_pcount);
   w->prefill_tiles = p.prefill_tiles;
+  w->prefill_longest = p.pitems.empty() ? 0 : (int)(p.pitems[0].tiles >> 16) - (int)(p.pitems[0].tiles & 0xffff);
 }
 
 // A masked stream the context already holds (no creation): the no-allocation path's lookup.

@@ -241,7 +241,9 @@ hipError_t launch_prefill_merge(const AttnArgs& a, const WorkArgs& w, hipStream_
 // that decode hardly matters (921,000 key tiles beside 1024 decode items: 0.6% slower in one launch;
 // 65,000 beside 1,100: 5% faster), nor for many small decode items, two of which fit on a CU that
 // runs no prefill (us a layer, one launch against two: 512 new tokens beside 32 items 25 / 34,
-// beside 1600 items 84 / 79; 64 tokens beside 800 items 33 / 32).
+// beside 1600 items 84 / 79; 64 tokens beside 800 items 33 / 32).  Heads of 64 keep the rule, though their
+// prefill alone may run two workgroups per CU (16 / 2 heads, 100 decodes: beside 8192 tokens 193 / 228,
+// beside 8192 after 8192 543 / 515).
 constexpr int kMixedMaxTilesPerItem = 256;
 constexpr int kMixedMaxSmallItems = 512;
 inline bool use_mixed(const WorkArgs& w) {

@@ -175,8 +175,10 @@ void decode_lists(const duet_shape* s, const duet_batch* b, int extra, bool step
 }
 
 // Work lists of a call over `layers` layers and `steps` decode steps (steps > 1: look-ahead),
-// and their offsets in the workspace.
-void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps, Plan* p, bool fill) {
+// and their offsets in the workspace, with partial_buffers (1 or 2) buffers of split-K partials: only
+// calls of one layer and one step can do with one.
+void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps, Plan* p, bool fill,
+                int partial_buffers = 2) {
   const int g = s->num_q_heads / s->num_kv_heads;
   p->group = g;
   p->prefill_id_cap = 0;
@@ -340,7 +342,7 @@ void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps,
   p->off_append = off;
   if (n_dreq > 0) off = align_up(off + (size_t)(steps - 1) * layers * sizeof(AppendJob));
   p->upload_bytes = off;
-  for (int b = 0; b < 2; ++b) {
+  for (int b = 0; b < partial_buffers; ++b) {
     p->off_pacc[b] = off;
     off = align_up(off + (size_t)max_items * g * s->head_dim * sizeof(float));
     p->off_pml[b] = off;
@@ -713,7 +715,7 @@ int find_stream(duet_ctx* ctx, int cus, int high_end, hipStream_t* out) {
   return DUET_OK;
 }
 
-// no_alloc: the workspace is the context's scratch, streams must exist, staging never grows and
+// no_alloc (one layer): the workspace is the context's scratch, streams must exist, staging never grows and
 // no profiling events are created (profiling is ignored).
 int attn_layers(duet_ctx* ctx, const duet_shape* shape, int layers, const void* const* q_l,
                 const void* const* k_l, const void* const* v_l, int64_t num_phys_pages, const int32_t* page_table,
@@ -725,7 +727,9 @@ int attn_layers(duet_ctx* ctx, const duet_shape* shape, int layers, const void* 
 
   std::lock_guard<std::mutex> lock(ctx->mu);
   Plan& p = ctx->plan;
-  plan_batch(shape, batch, layers, 1, &p, true);
+  // The scratch holds one buffer of partials: batches that decode_rule cuts twice as fine then need no
+  // more of it than with whole splits and two buffers.
+  plan_batch(shape, batch, layers, 1, &p, true, no_alloc ? 1 : 2);
   if (split.mode == DUET_SPLIT) snake_prefill_rounds(&p.pitems);
   if (workspace_bytes < p.total)
     return fail(DUET_EWORKSPACE, "%s %zu bytes, need %zu", no_alloc ? "scratch holds" : "workspace", workspace_bytes,

@@ -70,3 +70,20 @@ def test_noalloc_split_needs_existing_streams(ctx):
     with pytest.raises(duet.DuetError) as e:
         ctx.attn_mixed_batch_noalloc(q, kc, vc, pt, b.seq_meta, duet.CuSplit.split(64, 192))
     assert e.value.code == -1  # DUET_EINVAL: no stream was created for this split
+
+
+def test_noalloc_holds_short_decode_items_beside_many_pieces(ctx):
+    """A batch whose decode items are cut to 16 pages (512 items, groups of 16) beside 480 prefill pieces:
+    with whole items and two buffers of partials it needs 63.9 MiB, with the short ones 68.0 MiB.
+    The scratch holds it, since a call of one layer lays out one buffer."""
+    import paper_2511_04791_amd as duet
+    from paper_2511_04791_amd import workloads as wl
+    shape = wl.AttnShape(32, 2, 128, "bf16")
+    b = wl.make_batch(shape, [(1, 1, 1821)] * 32 + [(0, 576, 0), (0, 528, 0)] + [(0, 512, 8000)] * 6, page_seed=35)
+    assert duet.workspace_bytes(shape, b.seq_meta) > 66 << 20  # two buffers would not fit
+    q, kc, vc, pt = _tensors(b, 4303)
+    want = ctx.attn_mixed_batch(q, kc, vc, pt, b.seq_meta, duet.CuSplit.agg(), check_errors=True)
+    got = torch.full_like(q, float("nan"))
+    ctx.attn_mixed_batch_noalloc(q, kc, vc, pt, b.seq_meta, duet.CuSplit.agg(), out=got)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)

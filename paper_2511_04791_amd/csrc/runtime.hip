@@ -118,10 +118,12 @@ struct Plan {
 // descriptors (q_start, req | kv head << 24, first page | (tokens - 1) << 22, row of the split's
 // partial).  With step_rows (look-ahead steps), decode request i reads its query from row i.
 // A (request, kv head) range of n_pages pages is cut into splits of pps pages from page 0, the
-// last one short.
+// last one short.  *n_rows: items to lay out memory for.  A batch just past the short items' range has fewer
+// items than one just within it; it gets as many rows, so that a workspace sized for a larger batch
+// holds every smaller one.
 void decode_lists(const duet_shape* s, const duet_batch* b, int extra, bool step_rows, bool fill,
                   std::vector<int4>* dreq, std::vector<int4>* ditems, int64_t* n_dreq, int64_t* n_items,
-                  int* max_split, DecodeRule* rule) {
+                  int64_t* n_rows, int* max_split, DecodeRule* rule) {
   dreq->clear();
   ditems->clear();
   auto pages_of = [&](const duet_seq_meta& q) { return (int)(((int64_t)q.cached_len + q.q_len + extra + 15) / 16); };
@@ -147,6 +149,8 @@ void decode_lists(const duet_shape* s, const duet_batch* b, int extra, bool step
     if (fill) dreq->push_back(make_int4(r, (int)*n_items, n_split, pages_of(q)));
     *n_items += (int64_t)s->num_kv_heads * n_split;
   }
+  constexpr int kMostShort = kShortMaxItems * (kDecodePagesPerSplit / kDecodePagesPerSplitShort);
+  *n_rows = items > kShortMaxItems && s->dtype == DUET_BF16 && !rule->small ? std::max<int64_t>(*n_items, kMostShort) : *n_items;
   if (fill && s->dtype == DUET_BF16) {
     ditems->reserve(*n_items);
     struct Part {
@@ -294,9 +298,9 @@ void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps,
     p->pitems.reserve(tiles.size());
     for (const Tile& t : tiles) p->pitems.push_back(t.item);
   }
-  int64_t n_dreq = 0, n_items = 0;
+  int64_t n_dreq = 0, n_items = 0, n_rows = 0;
   int max_split = 0;
-  decode_lists(s, b, 0, false, fill, &p->dreq, &p->ditems, &n_dreq, &n_items, &max_split, &p->decode);
+  decode_lists(s, b, 0, false, fill, &p->dreq, &p->ditems, &n_dreq, &n_items, &n_rows, &max_split, &p->decode);
   p->n_items_decode = (int)n_items;
   p->max_split = max_split;
   size_t off = align_up(kCounterOffset + (size_t)kDecodeCounterInts * sizeof(int32_t));
@@ -307,14 +311,14 @@ void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps,
   p->off_dreq = off;
   off = align_up(off + (size_t)n_dreq * sizeof(int4));
   p->off_ditems = off;
-  off = align_up(off + (s->dtype == DUET_BF16 ? (size_t)n_items * sizeof(int4) : 0));
+  off = align_up(off + (s->dtype == DUET_BF16 ? (size_t)n_rows * sizeof(int4) : 0));
   p->off_punits = off;
   off = align_up(off + (size_t)n_pu * sizeof(PrefillUnit));
   p->off_pcount = off;  // zeroed by the upload
   off = align_up(off + (size_t)n_slots * sizeof(int32_t));
   // Look-ahead steps: each has its own metadata and decode lists; the split-K partials are
   // shared, since the steps run one after another on one stream.
-  int64_t max_items = n_items;
+  int64_t max_rows = n_rows;
   p->ahead.resize(steps - 1);
   for (int st = 1; st < steps; ++st) {
     StepPlan& sp = p->ahead[st - 1];
@@ -327,16 +331,16 @@ void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps,
         else sp.meta.push_back(make_int4(q.kind, q.q_start, q.q_len, q.cached_len));
       }
     }
-    int64_t nd = 0, ni = 0;
-    decode_lists(s, b, st, true, fill, &sp.dreq, &sp.ditems, &nd, &ni, &sp.max_split, &sp.decode);
+    int64_t nd = 0, ni = 0, nr = 0;
+    decode_lists(s, b, st, true, fill, &sp.dreq, &sp.ditems, &nd, &ni, &nr, &sp.max_split, &sp.decode);
     sp.n_items = (int)ni;
-    max_items = std::max(max_items, ni);
+    max_rows = std::max(max_rows, nr);
     sp.off_meta = off;
     off = align_up(off + (size_t)b->num_reqs * sizeof(int4));
     sp.off_dreq = off;
     off = align_up(off + (size_t)nd * sizeof(int4));
     sp.off_ditems = off;
-    off = align_up(off + (s->dtype == DUET_BF16 ? (size_t)ni * sizeof(int4) : 0));
+    off = align_up(off + (s->dtype == DUET_BF16 ? (size_t)nr * sizeof(int4) : 0));
   }
   p->append.clear();
   p->off_append = off;
@@ -344,9 +348,9 @@ void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps,
   p->upload_bytes = off;
   for (int b = 0; b < partial_buffers; ++b) {
     p->off_pacc[b] = off;
-    off = align_up(off + (size_t)max_items * g * s->head_dim * sizeof(float));
+    off = align_up(off + (size_t)max_rows * g * s->head_dim * sizeof(float));
     p->off_pml[b] = off;
-    off = align_up(off + (size_t)max_items * g * 2 * sizeof(float));
+    off = align_up(off + (size_t)max_rows * g * 2 * sizeof(float));
   }
   p->off_ppart = off;
   off = align_up(off + (size_t)n_slots * prefill_slot_bytes(s->head_dim));

@@ -80,6 +80,21 @@ def test_workspace_grows_with_decode_splits(native):
     assert c.value - a.value >= (59 - 1) * 8 * 4 * 130 * 4
 
 
+@pytest.mark.parametrize("heads", [(32, 8), (8, 1), (32, 2)])
+def test_workspace_of_a_longer_batch_holds_a_shorter_one(native, heads):
+    # batches of up to 256 split-K items are cut twice as fine: contexts that step over that line
+    # (and the one at 96 items) must not make the workspace smaller
+    for n_req in (3, 12, 16, 33, 64, 100):
+        last = 0
+        for ctx in range(200, 5200, 100):
+            arr, b = _batch([(1, i, 1, ctx) for i in range(n_req)])
+            n = ctypes.c_size_t()
+            sh = _shape(num_q_heads=heads[0], num_kv_heads=heads[1])
+            assert native.duet_workspace_bytes(ctypes.byref(sh), ctypes.byref(b), ctypes.byref(n)) == 0
+            assert n.value >= last, (n_req, ctx)
+            last = n.value
+
+
 def test_iteration_rejects_bad_layer_arguments(native):
     arr, b = _batch([(1, 0, 1, 10)])
     ptrs = (ctypes.c_void_p * 2)(1, 1)

@@ -335,7 +335,10 @@ int duet_attn_mixed_batch(duet_ctx* ctx, const duet_shape* shape, const void* q,
  * Under DUET_SPLIT or DUET_CONCURRENT the CU-masked streams must already exist: one earlier call
  * of duet_attn_mixed_batch or duet_attn_iteration with the same split creates them (the context
  * keeps the streams of its most recently used split or mode); otherwise DUET_EINVAL.  Profiling
- * is ignored.  The output is bit-identical to duet_attn_mixed_batch's.  Every call on a device shares that device's array,
+ * is ignored.  The output is bit-identical to duet_attn_mixed_batch's.  A call on a stream under
+ * capture carries its work lists inside the graph, so the graph may be replayed after other calls; it
+ * stays bound to the batch's lengths and to the pointers of the call, and reads queries, caches and
+ * page ids as each replay finds them.  Every call on a device shares that device's array,
  * which keeps the last call's contents (each call's upload clears the parts that must start at
  * zero): calls that overlap on one device, from any context or thread, race.  Page ids outside
  * the pool are never dereferenced; the error word they set lives in the scratch and is not

@@ -267,6 +267,9 @@ constexpr int kUploadBlocks = 64;
 int upload_blocks(size_t bytes);
 hipError_t launch_upload(const void* src, void* dst, size_t zero_bytes, size_t bytes, uint32_t* flags, uint32_t seq,
                          hipStream_t s);
+// Copies `bytes` (a multiple of 4) of host memory to dst as kernel arguments: src may change as soon as
+// the call returns, also where the launches are captured.
+hipError_t launch_upload_by_value(const void* src, void* dst, size_t bytes, hipStream_t s);
 
 hipError_t launch_read_probe(const void* buf, size_t bytes, int blocks, unsigned* sink, hipStream_t s);
 size_t read_probe_bytes(size_t bytes, int blocks);

@@ -69,7 +69,8 @@ static_assert(kScratchBytes == DUET_NOALLOC_SCRATCH_BYTES, "the header states th
   } while (0)
 
 // One pinned buffer of work lists: kUploadBlocks flags, then cap bytes.  Its reader is the upload
-// kernel, which sets the flags to seq, or a copy command, which `done` follows.
+// kernel, which sets the flags to seq, or (a workspace off a 16-byte boundary) a copy command,
+// which `done` follows.
 struct StagingSlot {
   char* host = nullptr;
   size_t cap = 0;
@@ -556,16 +557,8 @@ int alloc_slot(StagingSlot* slot, size_t cap) {
   return DUET_OK;
 }
 
-int stage_upload(duet_ctx* ctx, const Plan& p, char* ws, hipStream_t st, bool may_allocate = true) {
-  StagingSlot& slot = ctx->slots[ctx->next_slot];
-  if (!may_allocate && slot.cap < p.upload_bytes)
-    return fail(DUET_EWORKSPACE, "work lists of %zu bytes exceed the %zu bytes of preallocated staging", p.upload_bytes,
-                slot.cap);
-  ctx->next_slot = (ctx->next_slot + 1) % kStagingSlots;
-  int rc = wait_slot(&slot);
-  if (rc) return rc;
-  if (slot.cap < p.upload_bytes && (rc = alloc_slot(&slot, std::max<size_t>(p.upload_bytes * 2, 1 << 16)))) return rc;
-  char* h = slot.data();
+// The lists of a call as they lie in the workspace from off_meta on.
+void write_lists(const Plan& p, char* h) {
   std::memcpy(h + p.off_meta, p.meta.data(), p.meta.size() * sizeof(int4));
   std::memcpy(h + p.off_pitems, p.pitems.data(), p.pitems.size() * sizeof(PrefillItem));
   std::memcpy(h + p.off_dreq, p.dreq.data(), p.dreq.size() * sizeof(int4));
@@ -578,12 +571,29 @@ int stage_upload(duet_ctx* ctx, const Plan& p, char* ws, hipStream_t st, bool ma
     std::memcpy(h + sp.off_dreq, sp.dreq.data(), sp.dreq.size() * sizeof(int4));
     std::memcpy(h + sp.off_ditems, sp.ditems.data(), sp.ditems.size() * sizeof(int4));
   }
-  // A stream that is being captured records a copy, guarded by its event as any copy: the flags
-  // of a captured upload would be set by its replays only.
+}
+
+int stage_upload(duet_ctx* ctx, const Plan& p, char* ws, hipStream_t st, bool may_allocate = true) {
+  StagingSlot& slot = ctx->slots[ctx->next_slot];
+  if (!may_allocate && slot.cap < p.upload_bytes)
+    return fail(DUET_EWORKSPACE, "work lists of %zu bytes exceed the %zu bytes of preallocated staging", p.upload_bytes,
+                slot.cap);
   hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-  const bool known = hipStreamIsCapturing(st, &capturing) == hipSuccess;
-  if (!known) (void)hipGetLastError();
-  if (known && capturing == hipStreamCaptureStatusNone && reinterpret_cast<uintptr_t>(ws) % 16 == 0) {
+  HIP_TRY(hipStreamIsCapturing(st, &capturing));
+  if (capturing != hipStreamCaptureStatusNone) {
+    // No staging buffer: replays would find another call's lists in it.
+    std::vector<char> lists(p.upload_bytes);
+    write_lists(p, lists.data());
+    HIP_TRY(launch_upload_by_value(lists.data(), ws, p.upload_bytes, st));
+    return DUET_OK;
+  }
+  ctx->next_slot = (ctx->next_slot + 1) % kStagingSlots;
+  int rc = wait_slot(&slot);
+  if (rc) return rc;
+  if (slot.cap < p.upload_bytes && (rc = alloc_slot(&slot, std::max<size_t>(p.upload_bytes * 2, 1 << 16)))) return rc;
+  char* h = slot.data();
+  write_lists(p, h);
+  if (reinterpret_cast<uintptr_t>(ws) % 16 == 0) {
     slot.blocks = upload_blocks(p.upload_bytes);
     HIP_TRY(launch_upload(h, ws, p.off_meta, p.upload_bytes, slot.flags(), ++slot.seq, st));
     slot.reader = StagingSlot::kKernel;

@@ -1,5 +1,5 @@
 """How a call's work lists reach the device: a call waits for the staging of its own upload only, a
-workspace off a 16-byte boundary is served by a copy."""
+workspace off a 16-byte boundary is served by a copy, a captured call carries its lists in the graph."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -61,3 +61,35 @@ def test_workspace_off_a_16_byte_boundary(ctx):
     torch.cuda.synchronize()
     for i, g in enumerate(got):
         assert torch.equal(g, want[i % len(cases)]), i
+
+
+@pytest.mark.parametrize("noalloc", [True, False])
+def test_a_captured_call_replays_after_other_calls(ctx, noalloc):
+    """Replays between eager calls of other batches, which reuse every staging buffer, give the captured
+    batch's result for the queries of the moment.  Lists shorter and longer than one launch carries."""
+    import paper_2511_04791_amd as duet
+    for reqs in (((1, 1, 300), (0, 77, 19), (1, 1, 1200)), ((1, 1, 3000),) * 60 + ((0, 300, 100),)):
+        b, (q, kc, vc, pt) = _batch(5, reqs)
+        others = [_batch(6, ((1, 1, 4000), (0, 900, 40))), _batch(7, ((1, 1, 40),) * 9)]
+        ws = torch.empty(duet.workspace_bytes(duet.shape_of(q, kc), b.seq_meta), dtype=torch.uint8, device="cuda")
+        out = torch.empty_like(q)
+
+        def call():
+            if noalloc:
+                return ctx.attn_mixed_batch_noalloc(q, kc, vc, pt, b.seq_meta, out=out)
+            return ctx.attn_mixed_batch(q, kc, vc, pt, b.seq_meta, out=out, workspace=ws)
+
+        call()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            call()
+        for seed in range(4):
+            q.copy_(torch.randn(q.shape, generator=torch.Generator().manual_seed(seed)).to(q.dtype))
+            want = ctx.attn_mixed_batch(q, kc, vc, pt, b.seq_meta)
+            for ob, ox in others * 3:
+                ctx.attn_mixed_batch(*ox, ob.seq_meta)
+            out.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want), (len(reqs), seed)

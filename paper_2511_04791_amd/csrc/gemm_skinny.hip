@@ -275,6 +275,12 @@ hipError_t launch(const SkinnyArgs& a, hipStream_t s) {
 
 }  // namespace
 
+bool use_skinny(int rows, int cus, size_t weight_bytes, int widest, size_t bytes) {
+  if (rows < 1 || rows > kSkinnyRows || (size_t)rows * widest * sizeof(float) > bytes) return false;
+  if (cus == DUET_TOTAL_CUS || weight_bytes <= (size_t)64 << 20) return true;
+  return rows <= kSkinnyRows / 2 && cus >= 96 && weight_bytes <= (size_t)512 << 20;
+}
+
 // Parts of d_in: about one workgroup per CU of the whole chip (never per share, so results do
 // not depend on the split), each wave with a step of its own, partials within `bytes`.
 int skinny_splits(int rows, int d_in, int d_out, size_t bytes) {

@@ -197,7 +197,8 @@ struct QkvSplitArgs {
 };
 
 // Projections of few rows (gemm_skinny.hip) instead of the library's, for a partition of `rows` rows on
-// `cus` CUs whose layer holds `weight_bytes` of projection weights.  On the whole chip the own kernels
+// `cus` CUs whose layer holds `weight_bytes` of projection weights: where one part of its widest product,
+// [rows, widest] in fp32, fits in `bytes` (more than 131072 columns at 64 rows do not).  On the whole chip the own kernels
 // win for every size measured up to 64 rows (above).  On a share a CU pulls them at about 30 GB/s,
 // somewhat below the library's kernels, which show once nothing else is slower.  Us per layer, own
 // against the library's, on 128 / 96 / 64 / 32 CUs:
@@ -207,11 +208,7 @@ struct QkvSplitArgs {
 //   1.7 GB (Llama-3-70B), 16 rows: 541 / 682 / 887 / 1662 against 526 / 759 / 868 / 1424;
 //   12 MB (16 heads of 64), 64 rows: 72 / 72 / 73 / 83 against 95 / 93 / 94 / 94.
 constexpr int kSkinnyRows = 64;
-inline bool use_skinny(int rows, int cus, size_t weight_bytes) {
-  if (rows < 1 || rows > kSkinnyRows) return false;
-  if (cus == DUET_TOTAL_CUS || weight_bytes <= (size_t)64 << 20) return true;
-  return rows <= kSkinnyRows / 2 && cus >= 96 && weight_bytes <= (size_t)512 << 20;
-}
+bool use_skinny(int rows, int cus, size_t weight_bytes, int widest, size_t bytes);
 struct SkinnyArgs {
   const __bf16* x;  // [rows, d_in]
   const __bf16* w;  // [d_in, d_out]
@@ -219,6 +216,7 @@ struct SkinnyArgs {
   __bf16 *gu, *act; // gate-up: [rows, 2 m], [rows, m]
   int32_t rows, d_in, d_out, m, splits, tiles;
 };
+// At least one, whether or not one part fits in `bytes` (use_skinny).
 int skinny_splits(int rows, int d_in, int d_out, size_t bytes);
 hipError_t launch_skinny_gemm(const __bf16* x, const __bf16* w, float* part, int rows, int d_in, int d_out, int splits,
                               hipStream_t s);

@@ -1369,7 +1369,7 @@ int block_forward(duet_ctx* ctx, const duet_shape* shape, const duet_block_shape
     al.out = step_dreq ? ab + r0 * d : ab;
     // Few rows: own projection kernels, whose finishing kernels run the operator that follows; the
     // norm before a layer comes with the layer before it.
-    const bool skinny = weights_aligned && use_skinny(pt.rows, pt.cus, weight_bytes);
+    const bool skinny = weights_aligned && use_skinny(pt.rows, pt.cus, weight_bytes, std::max(d_qkv, d), kGemmWorkspaceBytes);
     float* part = static_cast<float*>(pt.gemm_ws);
     auto project = [&](const __bf16* in, const void* wm, int d_in, int d_out, int* splits) {
       *splits = skinny_splits(pt.rows, d_in, d_out, kGemmWorkspaceBytes);

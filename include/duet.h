@@ -406,6 +406,8 @@ int duet_block_workspace_bytes(const duet_shape* shape, const duet_block_shape* 
  * norm_eps > 0.  AGG runs everything on `stream`; SPLIT runs the decode requests' rows on the
  * decode CUs and the prefill requests' rows on the prefill CUs, each partition all layers back
  * to back, and needs each kind's rows to be one contiguous range (DUET_EUNSUPPORTED otherwise).
+ * The projections of a partition run on kernels chosen from its rows, the layer's weight bytes and its
+ * CUs, so the last bits of a block's result may differ between shares, and between AGG and SPLIT.
  * Requests must not share cache pages.  A page id outside [0, num_phys_pages) met while writing
  * or reading the cache is not dereferenced and sets the error word.  Stream, ownership and
  * validation rules as for duet_attn_iteration.  Look-ahead (Section 4.3): with

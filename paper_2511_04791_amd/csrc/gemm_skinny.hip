@@ -277,12 +277,14 @@ hipError_t launch(const SkinnyArgs& a, hipStream_t s) {
 
 bool use_skinny(int rows, int cus, size_t weight_bytes, int widest, size_t bytes) {
   if (rows < 1 || rows > kSkinnyRows || (size_t)rows * widest * sizeof(float) > bytes) return false;
-  if (cus == DUET_TOTAL_CUS || weight_bytes <= (size_t)64 << 20) return true;
-  return rows <= kSkinnyRows / 2 && cus >= 96 && weight_bytes <= (size_t)512 << 20;
+  if (cus == DUET_TOTAL_CUS) return true;
+  if (rows <= kSkinnyRows / 2 && cus >= 96) return weight_bytes <= (size_t)512 << 20;
+  const size_t tile_rows = rows <= 16 ? 16 : rows <= 32 ? 32 : 64;
+  return weight_bytes <= (size_t)64 << 20 && tile_rows * weight_bytes <= (size_t)18000000 * std::min(cus, 128);
 }
 
-// Parts of d_in: about one workgroup per CU of the whole chip (never per share, so results do
-// not depend on the split), each wave with a step of its own, partials within `bytes`.
+// Parts of d_in: about one workgroup per CU of the whole chip, each wave with a step of its own, partials
+// within `bytes`.  Never per share: every share that takes these kernels adds in the same order.
 int skinny_splits(int rows, int d_in, int d_out, size_t bytes) {
   const int tiles = (d_out + kTileCols - 1) / kTileCols;
   const int steps = (d_in + 31) / 32;

@@ -198,15 +198,27 @@ struct QkvSplitArgs {
 
 // Projections of few rows (gemm_skinny.hip) instead of the library's, for a partition of `rows` rows on
 // `cus` CUs whose layer holds `weight_bytes` of projection weights: where one part of its widest product,
-// [rows, widest] in fp32, fits in `bytes` (more than 131072 columns at 64 rows do not).  On the whole chip the own kernels
-// win for every size measured up to 64 rows (above).  On a share a CU pulls them at about 30 GB/s,
-// somewhat below the library's kernels, which show once nothing else is slower.  Us per layer, own
-// against the library's, on 128 / 96 / 64 / 32 CUs:
-//   0.44 GB (Llama-3-8B), 16 rows: 183 / 238 / 294 / 492 against 227 / 267 / 282 / 443;
-//                         32 rows: 211 / 282 / 357 / 613 against 274 / 325 / 412 / 649;
-//                         64 rows: 260 / 355 / 454 / 797 against 294 / 329 / 380 / 580;
-//   1.7 GB (Llama-3-70B), 16 rows: 541 / 682 / 887 / 1662 against 526 / 759 / 868 / 1424;
-//   12 MB (16 heads of 64), 64 rows: 72 / 72 / 73 / 83 against 95 / 93 / 94 / 94.
+// [rows, widest] in fp32, fits in `bytes` (more than 131072 columns at 64 rows do not).  On the whole
+// chip the own kernels win for every size measured up to 64 rows (above).  On a share they pull weights
+// at about 30 GB/s a CU, somewhat below the library's kernels, and past 32 rows their products grow with
+// the rows (16, 32 or 64), so they lose where rows times weights are large for the CUs.  Us per layer
+// of four, own against the library's, on 128 / 96 / 64 / 32 CUs (the library's calls cost the host about
+// 84 us a layer, which is what the smallest sizes show):
+//   436 MB (Llama-3-8B), 16 rows: 192 / 241 / 294 / 492 against 208 / 251 / 267 / 435;
+//                        32 rows: 212 / 285 / 357 / 613 against 256 / 312 / 399 / 648;
+//                        64 rows: 260 / 355 / 454 / 797 against 284 / 319 / 377 / 585;
+//   126 MB, 16 rows: 83 / 108 against 119 / 147 on 128 and 96 CUs;
+//   50 MB, 16 rows: 74 / 77 / 83 / 116 against 86 / 85 / 85 / 92;
+//          32 rows: 83 / 89 / 99 / 152 against 86 / 87 / 88 / 121;
+//          64 rows: 100 / 112 / 128 / 211 against 91 / 105 / 110 / 140;
+//   30 MB, 16 rows: 61 / 63 / 63 / 81 against 84 / 85 / 84 / 85;
+//          32 rows: 68 / 72 / 72 / 99 against 85 / 85 / 85 / 86;
+//          64 rows: 81 / 87 / 87 / 128 against 86 / 87 / 86 / 92;
+//   17 MB, 32 rows: 66 / 66 / 66 / 75 against 84 / 85 / 85 / 85;
+//          64 rows: 79 / 79 / 79 / 96 against 85 / 85 / 84 / 85;
+//   11 MB, 64 rows: 77 / 79 / 79 / 90 against 85 / 84 / 84 / 85.
+// The two round their sums in different orders, so a block's result may differ in its last bits between
+// shares on different sides of the rule.
 constexpr int kSkinnyRows = 64;
 bool use_skinny(int rows, int cus, size_t weight_bytes, int widest, size_t bytes);
 struct SkinnyArgs {

@@ -38,6 +38,16 @@ def test_partitions(ctx, share):  # noqa: F811
               duet.CuSplit.split(256 - share, share), 4500)
 
 
+@pytest.mark.parametrize("rows,cus", [(16, 256), (16, 128), (16, 64), (32, 96), (33, 96), (33, 256)])
+def test_large_weights_on_both_sides_of_the_rule(ctx, rows, cus):  # noqa: F811
+    """75 MB of weights a layer: own kernels aggregated and, up to 32 rows, on 96 CUs or more; the
+    library's on the other shares."""
+    import paper_2511_04791_amd as duet
+    from paper_2511_04791_amd import workloads as wl
+    split = duet.CuSplit.agg() if cus == 256 else duet.CuSplit.split(256 - cus, cus)
+    _run_case(ctx, [(1, 1, 9 + 7 * i) for i in range(rows)], 4096, 1, split, 4650 + rows, wl.AttnShape(16, 8, 128, "bf16"))
+
+
 def test_bad_page_is_flagged_and_not_written(ctx):  # noqa: F811
     import paper_2511_04791_amd as duet
     from paper_2511_04791_amd import workloads as wl

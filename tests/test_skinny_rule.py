@@ -35,3 +35,14 @@ def test_partials_fit_their_buffer(rule, splits):
                 for d_in, d_out in ((d, d_qkv), (d, d), (28672, d)):
                     assert splits(rows, d_in, d_out, BUFFER) * rows * d_out * 4 <= BUFFER, (kv, group, rows)
     assert refused  # 64 rows of 57 kv heads need 33.6 MB
+
+
+@pytest.mark.parametrize("rows,mb,cus,own", [
+    (1, 12, 8, False), (16, 29, 32, True), (16, 50, 32, False), (32, 17, 32, True), (32, 30, 32, False),
+    (33, 11, 32, False), (64, 9, 32, True), (16, 50, 64, True), (16, 75, 64, False), (32, 30, 64, True),
+    (32, 50, 64, False), (64, 17, 64, True), (64, 30, 64, False), (64, 17, 96, True), (64, 50, 128, False),
+    (64, 30, 128, True), (64, 50, 224, False), (32, 500, 96, True), (33, 500, 96, False), (32, 500, 88, False),
+    (32, 600, 224, False), (64, 1700, 256, True), (65, 1, 256, False), (0, 1, 256, False)])
+def test_both_sides_of_the_rule(rule, rows, mb, cus, own):
+    """On a share the own kernels run only where they were measured no slower than the library's."""
+    assert rule(rows, cus, mb * 1000000, 1024, BUFFER) == own

@@ -534,9 +534,11 @@ int wait_slot(StagingSlot* slot) {
         if (__atomic_load_n(slot->flags() + b, __ATOMIC_ACQUIRE) != slot->seq) return true;
       return false;
     };
-    for (int tries = 0; unread(); ++tries) {
-      if (tries < 1000) std::this_thread::yield();
-      else std::this_thread::sleep_for(std::chrono::microseconds(20));
+    // Calls in a row wait here for the fourth one before them: sleeping would leave the queue empty.
+    const auto start = std::chrono::steady_clock::now();
+    while (unread()) {
+      if (std::chrono::steady_clock::now() - start < std::chrono::milliseconds(100)) std::this_thread::yield();
+      else std::this_thread::sleep_for(std::chrono::microseconds(100));
     }
   }
   slot->reader = StagingSlot::kFree;

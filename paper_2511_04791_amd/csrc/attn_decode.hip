@@ -46,10 +46,10 @@ __global__ __launch_bounds__(256, 1) void decode_partial_bf16(AttnArgs a, WorkAr
   decode_stream<D, PPS>(a, w, stage[wave], 4 * blockIdx.x + wave, 4 * gridDim.x);
 }
 
-template <int D>
+template <int D, bool kPack>
 __global__ __launch_bounds__(kSmallThreads, 4) void decode_small_bf16(AttnArgs a, WorkArgs w) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
-  decode_item<D>(a, w, blockIdx.x, lds);
+  decode_items<D, kPack>(a, w, blockIdx.x, lds);
 }
 
 // Merges every (decode request, query head) pair of one layer: one wave per pair.
@@ -89,23 +89,25 @@ hipError_t launch_persistent(const AttnArgs& a, const WorkArgs& w, hipStream_t s
   return hipGetLastError();
 }
 
-template <int D>
+template <int D, bool kPack>
 hipError_t launch_small(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
   static bool attr_set = false;  // the attribute is per function and process
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_small_bf16<D>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&decode_small_bf16<D, kPack>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)small_lds_bytes<D>(16));
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  hipLaunchKernelGGL(decode_small_bf16<D>, dim3(w.n_ditems), dim3(kSmallThreads), small_lds_bytes<D>(a.group), s, a, w);
+  hipLaunchKernelGGL((decode_small_bf16<D, kPack>), dim3(small_blocks(w)), dim3(kSmallThreads), small_lds_bytes<D>(a.group), s, a, w);
   return hipGetLastError();
 }
 
 hipError_t launch_decode_partial(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
   if (w.n_dreq == 0) return hipSuccess;
   if (a.dtype != 0) return launch_decode_partial_f32(a, w, s);
-  if (w.decode_small) return a.head_dim == 128 ? launch_small<128>(a, w, s) : launch_small<64>(a, w, s);
+  if (w.decode_small && w.n_small8 < w.n_ditems)
+    return a.head_dim == 128 ? launch_small<128, true>(a, w, s) : launch_small<64, true>(a, w, s);
+  if (w.decode_small) return a.head_dim == 128 ? launch_small<128, false>(a, w, s) : launch_small<64, false>(a, w, s);
   if (w.decode_pps == kDecodePagesPerSplitShort)
     return a.head_dim == 128 ? launch_persistent<128, kDecodePagesPerSplitShort>(a, w, s)
                              : launch_persistent<64, kDecodePagesPerSplitShort>(a, w, s);

@@ -431,22 +431,25 @@ __device__ __forceinline__ void decode_stream(const AttnArgs& a, const WorkArgs&
 // chip does, since only three pages of it are in flight; eight waves with four pages each have
 // the whole item in flight, and the time is one descriptor, one page-id and one page latency, then
 // a merge of the waves through LDS.  Four requests of 620 .. 2783 tokens
-// (32 / 8 heads of 128): 26.7 us before, 10.8 us now.
+// (32 / 8 heads of 128): 26.7 us before, 10.8 us now.  Short items of a long list share a workgroup
+// (kernels.h, kSmallPair).
 constexpr int kSmallWaves = 8;
 constexpr int kSmallThreads = 64 * kSmallWaves;
 constexpr int kSmallPages = kDecodePagesPerSplit / kSmallWaves;
 static_assert(kSmallPages * kSmallWaves == kDecodePagesPerSplit, "the waves cover a split");
 static_assert(kSmallPages % 2 == 0, "values are consumed two pages at a time");
 
-// LDS of one workgroup: per wave the item's [g][D + 4] output and [g][2] (m, l); at most 68.6 KB (16
-// heads of 128).
+// LDS of one workgroup: per wave its item's [g][D + 4] output and [g][2] (m, l), and the descriptors of
+// its items; at most 68.7 KB (16 heads of 128).
+constexpr int kSmallMaxPack = 4;  // items of a workgroup
 template <int D>
 constexpr size_t small_lds_bytes(int g) {
-  return (size_t)kSmallWaves * g * (D + 4 + 2) * sizeof(float);
+  return (size_t)kSmallWaves * g * (D + 4 + 2) * sizeof(float) + kSmallMaxPack * sizeof(int4);
 }
 
-template <int D>
-__device__ __forceinline__ void decode_item(const AttnArgs& a, const WorkArgs& w, int index, float* const lds) {
+// Workgroup `block` of small_blocks(w).  kPack: some of the items share a workgroup.
+template <int D, bool kPack>
+__device__ __forceinline__ void decode_items(const AttnArgs& a, const WorkArgs& w, int block, float* const lds) {
   constexpr int P = kSmallPages;
   constexpr int kStride = D + 4;  // floats per head in LDS: heads start on different banks
   const int tid = threadIdx.x;
@@ -454,12 +457,30 @@ __device__ __forceinline__ void decode_item(const AttnArgs& a, const WorkArgs& w
   const int lane = tid & 63;
   const int col = lane & 15, quad = lane >> 4;
   const int g = a.group;
-  const DItem it = unpack_item(sload4(w.ditems + index), true);
-  const int n_pages = (it.n_tok + 15) >> 4;
+  // The workgroup's items first .. end - 1, W waves each.
+  int W = kSmallWaves, first = block, end = block + 1;
+  if (kPack && block >= w.n_small8) {
+    const int blocks4 = (w.n_small4 + 1) / 2;
+    if (block < w.n_small8 + blocks4) {
+      W = 4;
+      first = w.n_small8 + 2 * (block - w.n_small8);
+      end = min(first + 2, w.n_small8 + w.n_small4);
+    } else {
+      W = 2;
+      first = w.n_small8 + w.n_small4 + 4 * (block - w.n_small8 - blocks4);
+      end = min(first + 4, w.n_ditems);
+    }
+  }
+  const int sub = wave / W, wv = wave % W;  // the wave's item and its index among that item's waves
+  const bool has = first + sub < end;
+  const i32x4 desc = sload4(w.ditems + min(first + sub, end - 1));
+  const DItem it = unpack_item(desc, has);
+  const int n_tok = has ? it.n_tok : 0;  // a wave without an item: no page, no token
+  const int n_pages = (n_tok + 15) >> 4;
 
-  // Pages wave, wave + 8, ... of the item.
+  // Pages wv, wv + W, ... of the item.
   const int* prow = a.page_table + (size_t)it.req * a.max_pages + it.first_page;
-  const int mine = lane < P && wave + kSmallWaves * lane < n_pages ? prow[wave + kSmallWaves * lane] : 0;
+  const int mine = lane < P && wv + W * lane < n_pages ? prow[wv + W * lane] : 0;
   bf16x8 qf[D / 32];
   const __bf16* qrow = reinterpret_cast<const __bf16*>(a.q) + ((size_t)it.q_start * a.h_q + it.j * g + col) * D + quad * 8;
 #pragma unroll
@@ -468,7 +489,7 @@ __device__ __forceinline__ void decode_item(const AttnArgs& a, const WorkArgs& w
     qf[ks] = __builtin_bit_cast(bf16x8, u);
   }
   // Every key page and the first half of the value pages load at once; the other half follows the
-  // scores, so the wave fits in 128 registers and four workgroups in a CU.
+  // scores, so the wave fits in 128 registers and two workgroups in a CU.
   Page<D> pg[P];
   bool ok[P], bad = false;
   size_t slab[P];
@@ -483,7 +504,7 @@ __device__ __forceinline__ void decode_item(const AttnArgs& a, const WorkArgs& w
 #pragma unroll
   for (int u = 0; u < P; ++u) {
     const int id = __builtin_amdgcn_readlane(mine, u);
-    const bool there = wave + kSmallWaves * u < n_pages;
+    const bool there = wv + W * u < n_pages;
     ok[u] = there && page_ok(id, a.num_phys_pages);
     bad |= there && !ok[u];
     slab[u] = (size_t)(ok[u] ? id : 0) * a.h_kv + it.j;
@@ -512,7 +533,7 @@ __device__ __forceinline__ void decode_item(const AttnArgs& a, const WorkArgs& w
   for (int u = 0; u < P; ++u)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      if (!ok[u] || 16 * (wave + kSmallWaves * u) + 4 * quad + i >= it.n_tok) sc[u][i] = -INFINITY;
+      if (!ok[u] || 16 * (wv + W * u) + 4 * quad + i >= n_tok) sc[u][i] = -INFINITY;
       mx = fmaxf(mx, sc[u][i]);
     }
   const float m = max_rows(mx) * a.scale_log2;
@@ -539,7 +560,7 @@ __device__ __forceinline__ void decode_item(const AttnArgs& a, const WorkArgs& w
     uint64_t mk[2];
 #pragma unroll
     for (int x = 0; x < 2; ++x)  // values past the end must not reach the MFMA (0 x NaN is NaN)
-      mk[x] = low_elems_mask(it.n_tok - (16 * (wave + kSmallWaves * (u + x)) + 4 * quad));
+      mk[x] = low_elems_mask(n_tok - (16 * (wv + W * (u + x)) + 4 * quad));
     const bf16x8 pf = {pb[u][0], pb[u][1], pb[u][2], pb[u][3], pb[u + 1][0], pb[u + 1][1], pb[u + 1][2], pb[u + 1][3]};
 #pragma unroll
     for (int n = 0; n < D / 16; ++n) {
@@ -552,6 +573,8 @@ __device__ __forceinline__ void decode_item(const AttnArgs& a, const WorkArgs& w
   if (bad && lane == 0) atomicOr(w.err, 1);
 
   float* const ml = lds + kSmallWaves * g * kStride;  // [wave][g][2]
+  i32x4* const descs = reinterpret_cast<i32x4*>(ml + kSmallWaves * g * 2);
+  if (kPack && wv == 0 && lane == 0) descs[sub] = desc;
   if (col < g) {
     float* st = lds + (wave * g + col) * kStride;
 #pragma unroll
@@ -559,32 +582,38 @@ __device__ __forceinline__ void decode_item(const AttnArgs& a, const WorkArgs& w
     if (quad == 0) *reinterpret_cast<float2*>(ml + (wave * g + col) * 2) = make_float2(m, l);
   }
   __syncthreads();
-  // The waves in order, against their common max, one thread per four dims: the item's partial,
+  // An item's waves in order, against their common max, one thread per four dims: the item's partial,
   // or the output itself where no request has a second split (there is no reduce kernel then).
-  for (int x = tid; x < g * D / 4; x += kSmallThreads) {
-    const int c = x / (D / 4), e = 4 * (x % (D / 4));
+  for (int x = tid; x < (end - first) * g * D / 4; x += kSmallThreads) {
+    const int row = x / (D / 4), e = 4 * (x % (D / 4));
+    const int s = kPack ? row / g : 0, c = row - s * g;
+    const DItem t = kPack ? unpack_item(descs[s], true) : it;
+    const float* const ml_s = ml + (s * W * g + c) * 2;
+    const float* const acc_s = lds + (s * W * g + c) * kStride + e;
     float mm = -INFINITY;
 #pragma unroll
-    for (int v = 0; v < kSmallWaves; ++v) mm = fmaxf(mm, ml[(v * g + c) * 2]);
+    for (int v = 0; v < kSmallWaves; ++v)
+      if (v < W) mm = fmaxf(mm, ml_s[v * g * 2]);
     const float mm_sub = mm == -INFINITY ? 0.f : mm;
     float den = 0.f;
     f32x4 num = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int v = 0; v < kSmallWaves; ++v) {
-      const float2 t = *reinterpret_cast<const float2*>(ml + (v * g + c) * 2);
-      const float wgt = fast_exp2(t.x - mm_sub);
-      den += wgt * t.y;
-      num += wgt * *reinterpret_cast<const f32x4*>(lds + (v * g + c) * kStride + e);
+      if (v >= W) break;
+      const float2 p = *reinterpret_cast<const float2*>(ml_s + v * g * 2);
+      const float wgt = fast_exp2(p.x - mm_sub);
+      den += wgt * p.y;
+      num += wgt * *reinterpret_cast<const f32x4*>(acc_s + (size_t)v * g * kStride);
     }
     if (w.max_split == 1) {
       const float inv = 1.0f / den;
       bf16x4 o;
 #pragma unroll
       for (int i = 0; i < 4; ++i) o[i] = static_cast<__bf16>(num[i] * inv);
-      *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(a.out) + ((size_t)it.q_start * a.h_q + it.j * g) * D + 4 * x) = o;
+      *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(a.out) + ((size_t)t.q_start * a.h_q + t.j * g + c) * D + e) = o;
     } else {
-      *reinterpret_cast<f32x4*>(w.pacc + (size_t)it.slot * g * D + 4 * x) = num;
-      if (e == 0) *reinterpret_cast<float2*>(w.pml + ((size_t)it.slot * g + c) * 2) = make_float2(mm, den);
+      *reinterpret_cast<f32x4*>(w.pacc + ((size_t)t.slot * g + c) * D + e) = num;
+      if (e == 0) *reinterpret_cast<float2*>(w.pml + ((size_t)t.slot * g + c) * 2) = make_float2(mm, den);
     }
   }
 }

@@ -39,7 +39,7 @@ static_assert(decode::small_lds_bytes<128>(16) <= kRingBytes<128> && decode::sma
               "a small item fits");
 static_assert(decode::kSmallThreads == prefill::kThreads, "one workgroup size");
 
-// PPS: pages of a streamed decode item; 0: small items.
+// PPS: pages of a streamed decode item; 0: small items, -1: of which some share a workgroup.
 template <int D, int NH, int PPS>
 __global__ __launch_bounds__(prefill::kThreads, 2) void mixed_bf16(AttnArgs a, WorkArgs w, int decode_blocks) {
   extern __shared__ __attribute__((aligned(16))) __bf16 lds[];
@@ -49,8 +49,8 @@ __global__ __launch_bounds__(prefill::kThreads, 2) void mixed_bf16(AttnArgs a, W
     return;
   }
   float* const fl = reinterpret_cast<float*>(lds);
-  if constexpr (PPS == 0) {
-    decode::decode_item<D>(a, w, b, fl);
+  if constexpr (PPS <= 0) {
+    decode::decode_items<D, PPS < 0>(a, w, b, fl);
   } else {
     if (b == 0) decode::clear_previous_counters(w);
     const int wave = uniform(threadIdx.x >> 6);
@@ -72,9 +72,9 @@ hipError_t launch(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
     attr_set = true;
   }
   // Streamed: multiples of 8 (one per XCD), and at least two items for each of the first waves.
-  const int first = PPS == 0 ? w.n_ditems
+  const int first = PPS <= 0 ? small_blocks(w)
                              : std::max(8, std::min(kMixedDecodeBlocks<D>, w.n_ditems / (2 * kMixedWaves) / 8 * 8));
-  const int late = PPS == 0 ? 0 : std::max(0, w.decode_cus - first);
+  const int late = PPS <= 0 ? 0 : std::max(0, w.decode_cus - first);
   hipLaunchKernelGGL((mixed_bf16<D, NH, PPS>), dim3(first + w.n_pitems + late), dim3(prefill::kThreads),
                      Smem::bytes(w.prefill_id_cap), s, a, w, first);
   return hipGetLastError();
@@ -82,7 +82,7 @@ hipError_t launch(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
 
 template <int D, int NH>
 hipError_t launch_pps(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
-  if (w.decode_small) return launch<D, NH, 0>(a, w, s);
+  if (w.decode_small) return w.n_small8 < w.n_ditems ? launch<D, NH, -1>(a, w, s) : launch<D, NH, 0>(a, w, s);
   if (w.decode_pps == kDecodePagesPerSplitShort) return launch<D, NH, kDecodePagesPerSplitShort>(a, w, s);
   return launch<D, NH, kDecodePagesPerSplit>(a, w, s);
 }

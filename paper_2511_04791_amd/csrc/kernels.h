@@ -61,6 +61,7 @@ struct WorkArgs {
   int32_t n_pitems, n_dreq, max_split, n_ditems;
   int32_t decode_pps;     // pages per bf16 decode item
   int32_t decode_small;   // bf16 decode items run one workgroup each and merge themselves (decode_rule)
+  int32_t n_small8, n_small4;  // of those items, longest first: run with 8 waves, with 4; the rest with 2
   int32_t decode_cus;   // CUs the decode stream may use (sizes the persistent grid)
   int32_t prefill_cus;  // CUs the prefill stream may use
   int32_t prefill_id_cap;  // most pages of any prefill request (sizes the LDS page-id table)
@@ -72,6 +73,10 @@ struct WorkArgs {
   long long prefill_tiles;      // key tiles over all units (bf16)
   int32_t prefill_longest;      // key tiles of the longest item (bf16)
 };
+
+inline int small_blocks(const WorkArgs& w) {
+  return w.n_small8 + (w.n_small4 + 1) / 2 + (w.n_ditems - w.n_small8 - w.n_small4 + 3) / 4;
+}
 
 // Cache writes of look-ahead decode steps: new key and value rows in, paged cache out.  Job x writes step
 // x / layers + 1 of layer x % layers.
@@ -114,9 +119,10 @@ constexpr int kDecodeCounterInts = 2 * kDecodeSetInts;
 // every CU split; where two cuts trade the shares against each other, it takes the one that loses on
 // none of them by more than a few per cent.  Decode time of one layer (us), 32 / 8 heads of 128,
 // on 256, 128 and 32 CUs:
-//   one split per request: a workgroup per item wins throughout (contexts of 300 tokens, 64 items
+//   one split per request: a workgroup per item wins (contexts of 300 tokens, 64 items
 //     8.8 / 17 / 17 against 20.6 / 24 / 24 streamed; 512 items 18.8 / 29 / 79 against
-//     26.7 / 34 / 91; 4096 items 117 / 175 / 565 against 146 / 203 / 670);
+//     26.7 / 34 / 91; 4096 items 117 / 175 / 565 against 146 / 203 / 670), if short items share
+//     one (below);
 //   few items: a workgroup per item (contexts of 2048, 64 items 13.4 / 19.0 / 23.5 against
 //     28.0 / 31.5 / 31.5; from 128 items on 32 CUs lose, 37.4 against 34.3);
 //   then half as long items, streamed (128 items 18.6 / 22.2 / 34.6 against 29.1 / 32.9 / 34.3; 256
@@ -125,14 +131,25 @@ constexpr int kDecodeCounterInts = 2 * kDecodeSetInts;
 constexpr int kDecodePagesPerSplitShort = 16;
 constexpr int kSmallMaxItems = 96;
 constexpr int kShortMaxItems = 256;
+// A workgroup's eight waves take four pages each, so a short item alone leaves most of them without one,
+// which costs nothing while every CU has at most one item and a lot on small shares of long lists.  From
+// kSmallPair items on those of at most 16 pages run two to a workgroup, from kSmallQuad on those of at
+// most 8 pages four (fewer, and the whole chip would idle).  One layer of 16 (us), 16 / 8 heads of 128,
+// on 256, 96 and 32 CUs, streamed, a workgroup each, shared: contexts of 100 to 127, 512 items
+// 14.7 / 22.2 / 45, 10.8 / 24.2 / 54, 10.5 / 19 / 35; 1024 items 22 / 36 / 82, 19 / 40 / 101, 15 / 26 / 56;
+// 4000 items 63 / 111 / 294, 60 / 133 / 371, 48 / 81 / 201; contexts of 60 to 200, 4000 items 67 / 121 / 324,
+// 63 / 135 / 374, 52 / 85 / 218.  At 256 items sharing loses on the whole chip (contexts of 30 to 60
+// 5.6 against 6.4) and a workgroup each on 32 CUs only a little against streaming (100 to 127: 27.5 against 26.4).
+constexpr int kSmallPair = 257, kSmallQuad = 1024;
 struct DecodeRule {
   int pages_per_split;
-  bool small;  // decode_small_bf16: one workgroup per item
+  bool small;  // decode_small_bf16: one workgroup per item, or per 2 or 4 short ones
+  int n8, n4;  // of its items, longest first: run with 8 waves, with 4; the rest with 2
 };
 inline DecodeRule decode_rule(int64_t n_items, int max_pages) {
-  if (max_pages <= kDecodePagesPerSplit || n_items <= kSmallMaxItems) return {kDecodePagesPerSplit, true};
-  if (n_items <= kShortMaxItems) return {kDecodePagesPerSplitShort, false};
-  return {kDecodePagesPerSplit, false};
+  if (max_pages <= kDecodePagesPerSplit || n_items <= kSmallMaxItems) return {kDecodePagesPerSplit, true, 0, 0};
+  if (n_items <= kShortMaxItems) return {kDecodePagesPerSplitShort, false, 0, 0};
+  return {kDecodePagesPerSplit, false, 0, 0};
 }
 
 // Keys a prefill request may attend (its page ids are staged in LDS: 8192 ids, 32 KB).

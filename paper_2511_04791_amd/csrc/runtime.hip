@@ -139,7 +139,7 @@ void decode_lists(const duet_shape* s, const duet_batch* b, int extra, bool step
     items += (int64_t)s->num_kv_heads * ((pages_of(q) + pps - 1) / pps);
     max_pages = std::max(max_pages, pages_of(q));
   }
-  *rule = s->dtype == DUET_BF16 ? decode_rule(items, max_pages) : DecodeRule{pps, false};
+  *rule = s->dtype == DUET_BF16 ? decode_rule(items, max_pages) : DecodeRule{pps, false, 0, 0};
   pps = rule->pages_per_split;
   *max_split = (max_pages + pps - 1) / pps;
   *n_items = 0;
@@ -176,7 +176,19 @@ void decode_lists(const duet_shape* s, const duet_batch* b, int extra, bool step
     }
     std::stable_sort(parts.begin(), parts.end(), [](const Part& x, const Part& y) { return x.pages > y.pages; });
     for (const Part& pt : parts) ditems->push_back(pt.item);
+    for (const int4& it : *ditems) {
+      const int pages = ((int)((unsigned)it.z >> 22) + 16) >> 4;
+      if (pages > 16 || *n_items < kSmallPair) ++rule->n8;
+      else if (pages > 8 || *n_items < kSmallQuad) ++rule->n4;
+    }
   }
+}
+
+void set_decode(WorkArgs* w, const DecodeRule& r) {
+  w->decode_small = r.small;
+  w->decode_pps = r.pages_per_split;
+  w->n_small8 = r.n8;
+  w->n_small4 = r.n4;
 }
 
 // Work lists of a call over `layers` layers and `steps` decode steps (steps > 1: look-ahead),
@@ -410,7 +422,7 @@ void append_key(std::vector<uint64_t>* k, const DecodeLaunch& l) {
                         bits(w.pitems), bits(w.dreq), bits(w.pacc), bits(w.pml), bits(w.ditems), bits(w.err),
                         bits(w.work_counter), bits(w.clear_counter), bits(w.merge_pacc), bits(w.merge_pml),
                         bits(w.merge_out), bits(w.n_merge), bits(w.n_pitems), bits(w.n_dreq), bits(w.max_split),
-                        bits(w.n_ditems), bits(w.decode_small), bits(w.decode_pps), bits(w.decode_cus), bits(w.prefill_cus), bits(w.prefill_id_cap),
+                        bits(w.n_ditems), bits(w.decode_small), bits(w.decode_pps), bits(w.n_small8), bits(w.n_small4), bits(w.decode_cus), bits(w.prefill_cus), bits(w.prefill_id_cap),
                         bits(w.ppart), bits(w.punits), bits(w.n_punits), bits(w.pcount), bits(w.prefill_tiles), bits(w.prefill_longest),
                         bits(p.jobs), bits(p.page_table), bits(p.num_phys_pages), bits(p.max_pages), bits(p.h_kv),
                         bits(p.head_dim), bits(p.dtype), bits(p.first_job), bits(p.n_jobs), bits(p.layers)};
@@ -697,8 +709,7 @@ void base_args(const duet_ctx* ctx, const duet_shape* shape, const Plan& p, char
   w->err = reinterpret_cast<int32_t*>(ws);
   w->work_counter = reinterpret_cast<int32_t*>(ws + kCounterOffset);
   w->n_ditems = (int)p.ditems.size();
-  w->decode_small = p.decode.small;
-  w->decode_pps = p.decode.pages_per_split;
+  set_decode(w, p.decode);
   w->decode_cus = split.mode == DUET_SPLIT ? split.cus_decode : ctx->num_cus;
   w->prefill_cus = split.mode == DUET_SPLIT ? split.cus_prefill : ctx->num_cus;
   w->n_pitems = (int)p.pitems.size();
@@ -1061,8 +1072,7 @@ int attn_lookahead(duet_ctx* ctx, const duet_shape* shape, const void* const* q_
       ws_w.n_dreq = (int)spl.dreq.size();
       ws_w.n_ditems = (int)spl.ditems.size();
       ws_w.max_split = spl.max_split;
-      ws_w.decode_small = spl.decode.small;
-      ws_w.decode_pps = spl.decode.pages_per_split;
+      set_decode(&ws_w, spl.decode);
     }
     for (int l = 0; l < layers; ++l) {
       const int x = (st - 1) * layers + l;
@@ -1441,8 +1451,7 @@ int block_forward(duet_ctx* ctx, const duet_shape* shape, const duet_block_shape
     wl.n_dreq = (int)spl.dreq.size();
     wl.n_ditems = (int)spl.ditems.size();
     wl.max_split = spl.max_split;
-    wl.decode_small = spl.decode.small;
-    wl.decode_pps = spl.decode.pages_per_split;
+    set_decode(&wl, spl.decode);
     for (int l = 0; l < layers; ++l)
       if ((rc = run_layer(dpart, l, static_cast<__bf16*>(x_ahead[st - 1]), wl, wl.dreq))) return rc;
     if (prof && forked) HIP_TRY(hipEventRecord(ctx->ev_step[st + 1], dpart.st));

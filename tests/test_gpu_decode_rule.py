@@ -1,7 +1,7 @@
 """GPU parity of the bf16 decode kernels around the sizes where the decode rule changes the kernel.
 
-The rule counts items of 32 pages (512 tokens): one workgroup per item where no request has a second
-split or at most 96 items are there, streamed items of 16 pages up to 256 items, of 32 pages above.
+The rule counts items of 32 pages (512 tokens): one workgroup per item (or per two or four short ones of a
+long list) where no request has a second split or at most 96 items are there, streamed items of 16 pages up to 256 items, of 32 pages above.
 Against the fp64 oracle with the bf16 bounds, and bit for bit across CU splits.
 """
 import numpy as np
@@ -33,6 +33,13 @@ CASES = {
     "one split, three heads": ((6, 2, 64), EDGES),
     "one split, sixteen heads": ((16, 1, 128), EDGES),
     "one split, many items": ((8, 2, 64), [200 + 7 * i % 311 for i in range(260)]),
+    # short items that share a workgroup: 16 pages and fewer from 257 items on, 8 and fewer from 1024
+    "256 short items": ((8, 8, 64), [1 + 9 * i % 300 for i in range(32)]),
+    "pairs, an odd one": ((16, 1, 128), EDGES + [1 + 13 * i % 256 for i in range(245)]),
+    "pairs only": ((8, 2, 128), [1 + 7 * i % 200 for i in range(130)]),
+    "1023 items": ((6, 3, 64), [1 + 11 * i % 140 for i in range(341)]),
+    "fours, one over": ((4, 4, 128), EDGES + [1 + 5 * i % 128 for i in range(245)]),
+    "fours, two and three over": ((6, 2, 64), EDGES[3:] + [1 + 5 * i % 129 for i in range(508)]),
     "second split": ((8, 2, 128), EDGES + [513, 1024, 1025, 4000]),
     "96 items": ((8, 2, 128), [600] * 24),
     "97 items": ((8, 1, 128), [600] * 48 + [512]),
@@ -51,6 +58,7 @@ def test_decode_rule_edges(ctx, name):
     q, kc, vc = (t.cuda() for t in wl.make_tensors(b, 5000, scale=1.0))  # scores of unit variance
     pt = torch.as_tensor(b.page_table, device="cuda")
     out = ctx.attn_mixed_batch(q, kc, vc, pt, b.seq_meta, check_errors=True)
+    assert torch.isfinite(out).all()
     for sp in (duet.CuSplit.split(128, 128), duet.CuSplit.split(224, 32)):
         other = ctx.attn_mixed_batch(q, kc, vc, pt, b.seq_meta, sp, check_errors=True)
         torch.cuda.synchronize()
@@ -100,3 +108,19 @@ def test_small_decode_bad_page_is_flagged(ctx):
     out = ctx.attn_mixed_batch(q, kc, vc, pt, b.seq_meta, check_errors=True)
     torch.cuda.synchronize()
     assert errors(out, oracle_out(b, q, kc, vc))[0] <= BF16_MAX_ABS
+
+
+def test_short_items_beside_a_chunk(ctx):
+    """Aggregated, items that share a workgroup run in one launch with the chunk: same bits as split."""
+    import paper_2511_04791_amd as duet
+    from paper_2511_04791_amd import workloads as wl
+    for n in (130, 245):  # 260 and 490 items
+        b = wl.make_batch(wl.AttnShape(8, 2, 128, "bf16"), [(1, 1, 3 * i % 300) for i in range(n)] + [(0, 300, 70)], page_seed=301)
+        q, kc, vc = (t.cuda() for t in wl.make_tensors(b, 5001, scale=1.0))
+        pt = torch.as_tensor(b.page_table, device="cuda")
+        out = ctx.attn_mixed_batch(q, kc, vc, pt, b.seq_meta, check_errors=True)
+        other = ctx.attn_mixed_batch(q, kc, vc, pt, b.seq_meta, duet.CuSplit.split(128, 128), check_errors=True)
+        torch.cuda.synchronize()
+        assert torch.equal(out, other)
+        mx, mean = errors(out, oracle_out(b, q, kc, vc))
+        assert mx <= BF16_MAX_ABS and mean <= BF16_MEAN_ABS

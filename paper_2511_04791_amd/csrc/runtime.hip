@@ -1094,9 +1094,16 @@ int attn_lookahead(duet_ctx* ctx, const duet_shape* shape, const void* const* q_
         dl.ap = AppendArgs{};
         dl.w = ws_w;
       }
-      // bf16 merges are deferred as in attn_layers, within the step: the next step's splits differ (8 steps,
-      // 2 layers, 16 requests of 512 to 4096 tokens, 32 / 8 heads of 128: 512 us without, 489 with).
-      const bool defer = independent && shape->dtype == DUET_BF16 && !dl.w.decode_small;
+      // bf16 merges are deferred as in attn_layers, within the step (the next step's splits differ), where the
+      // streaming waves have few to take: four waves a CU merge their pairs one after the other, a
+      // kernel of its own has a wave for each.  A call of 6 steps of 8 layers (us), with and without
+      // deferring: 16 requests of 500 to 4000 tokens (32 / 8 heads) on 256, 64 and 32 CUs (2, 8 and 16
+      // pairs a CU) 1751 / 1862, 3077 / 3261 and 5300 / 5429; 64 of 600 to 2000 on 128, 96 and 64 (16, 21
+      // and 32) 4156 / 4223, 5083 / 5058 and 6943 / 6739; 200 of 530 to 700 (64 / 8 heads) on 32 (400)
+      // 26445 / 20408, but on 256 (25, 32 / 8 heads) 5370 / 5404.
+      constexpr int kDeferPairsPerCu = 25;
+      const bool defer = independent && shape->dtype == DUET_BF16 && !dl.w.decode_small &&
+                         (int64_t)w.n_dreq * a.h_q <= (int64_t)kDeferPairsPerCu * w.decode_cus;
       if (defer) {
         const int cur = l & 1, prev = cur ^ 1;
         dl.w.pacc = reinterpret_cast<float*>(ws + p.off_pacc[cur]);

@@ -69,3 +69,30 @@ def test_lookahead_rows_and_caches_in_use(mode, kind, alias):
             assert torch.equal(torch.nan_to_num(got.float()), torch.nan_to_num(want.float()))
     finally:
         ctx.close()
+
+
+def test_merges_deferred_and_not():
+    """17 requests of 32 heads: 544 pairs to merge are deferred into the next layer's kernel on 24 CUs and
+    more, merged by a kernel of their own on 16 and 8.  Same bits."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2511_04791_amd as duet
+    from paper_2511_04791_amd import workloads as wl
+    k, L = 3, 3
+    b = wl.make_batch(wl.LLAMA3_8B, [(1, 1, 500 + 90 * i) for i in range(17)], page_seed=7102, reserve_tokens=k)
+    qs, kcs, vcs = zip(*[[t.cuda() for t in wl.make_tensors(b, 7400 + l, device="cpu")] for l in range(L)])
+    ahead = [[t.cuda() for t in ts] for ts in wl.make_lookahead_tensors(b, k, 7500, device="cpu")]
+    qa, ka, va = [[ts[s] for s in range(k - 1) for _ in range(L)] for ts in ahead]
+    pt = torch.as_tensor(b.page_table, device="cuda")
+    ctx = duet.Context(0)
+    try:
+        got = []
+        for cus in (0, 128, 24, 16, 8):
+            sp = duet.CuSplit.split(256 - cus, cus, k) if cus else duet.CuSplit.agg(k)
+            outs, outs_a = ctx.attn_lookahead(list(qs), qa, ka, va, list(kcs), list(vcs), pt, b.seq_meta, sp, check_errors=True)
+            torch.cuda.synchronize()
+            got.append(torch.cat([t.flatten() for t in outs + outs_a]))
+        assert torch.isfinite(got[0]).all()
+        assert all(torch.equal(g, got[0]) for g in got[1:])
+    finally:
+        ctx.close()

@@ -419,14 +419,25 @@ void append_key(std::vector<uint64_t>* k, const DecodeLaunch& l) {
   const uint64_t f[] = {(uint64_t)l.kind, bits(a.q), bits(a.k_cache), bits(a.v_cache), bits(a.page_table),
                         bits(a.out), bits(a.num_phys_pages), bits(a.max_pages), bits(a.h_q), bits(a.h_kv),
                         bits(a.group), bits(a.head_dim), bits(a.dtype), bits(a.scale_log2), bits(w.meta),
-                        bits(w.pitems), bits(w.dreq), bits(w.pacc), bits(w.pml), bits(w.ditems), bits(w.err),
+                        bits(w.dreq), bits(w.pacc), bits(w.pml), bits(w.ditems), bits(w.err),
                         bits(w.work_counter), bits(w.clear_counter), bits(w.merge_pacc), bits(w.merge_pml),
-                        bits(w.merge_out), bits(w.n_merge), bits(w.n_pitems), bits(w.n_dreq), bits(w.max_split),
-                        bits(w.n_ditems), bits(w.decode_small), bits(w.decode_pps), bits(w.n_small8), bits(w.n_small4), bits(w.decode_cus), bits(w.prefill_cus), bits(w.prefill_id_cap),
-                        bits(w.ppart), bits(w.punits), bits(w.n_punits), bits(w.pcount), bits(w.prefill_tiles), bits(w.prefill_longest),
+                        bits(w.merge_out), bits(w.n_merge), bits(w.n_dreq), bits(w.max_split),
+                        bits(w.n_ditems), bits(w.decode_small), bits(w.decode_pps), bits(w.n_small8), bits(w.n_small4), bits(w.decode_cus),
                         bits(p.jobs), bits(p.page_table), bits(p.num_phys_pages), bits(p.max_pages), bits(p.h_kv),
                         bits(p.head_dim), bits(p.dtype), bits(p.first_job), bits(p.n_jobs), bits(p.layers)};
   k->insert(k->end(), std::begin(f), std::end(f));
+}
+
+// A decode launch reads nothing of the prefill half: without it, the graph of a decode step serves the
+// next call whatever has become of the chunk.
+WorkArgs decode_only(WorkArgs w) {
+  w.pitems = nullptr;
+  w.ppart = nullptr;
+  w.pcount = nullptr;
+  w.punits = nullptr;
+  w.n_pitems = w.n_punits = w.prefill_cus = w.prefill_id_cap = w.prefill_longest = 0;
+  w.prefill_tiles = 0;
+  return w;
 }
 
 // Word-wise multiply-xor hash (a lookup index only: a hit is confirmed by comparing the keys).
@@ -1082,17 +1093,17 @@ int attn_lookahead(duet_ctx* ctx, const duet_shape* shape, const void* const* q_
       dl.a.k_cache = kc_l[l];
       dl.a.v_cache = vc_l[l];
       dl.a.out = st == 0 ? out_l[l] : out_ahead[x];
-      dl.w = ws_w;
+      dl.w = decode_only(ws_w);
       dl.ap = AppendArgs{};
       if (st > 0 && !independent) {
         dl.ap = append;
         dl.ap.first_job = x;
         dl.ap.n_jobs = 1;
-        dl.w = w;
+        dl.w = decode_only(w);
         dl.kind = DecodeLaunch::kAppend;
         launches.push_back(dl);
         dl.ap = AppendArgs{};
-        dl.w = ws_w;
+        dl.w = decode_only(ws_w);
       }
       // bf16 merges are deferred as in attn_layers, within the step (the next step's splits differ), where the
       // streaming waves have few to take: four waves a CU merge their pairs one after the other, a
@@ -1137,7 +1148,7 @@ int attn_lookahead(duet_ctx* ctx, const duet_shape* shape, const void* const* q_
         DecodeLaunch dl;
         dl.kind = DecodeLaunch::kAppend;
         dl.a = a;
-        dl.w = w;
+        dl.w = decode_only(w);
         dl.ap = append;
         launches.push_back(dl);
       }

@@ -96,3 +96,34 @@ def test_merges_deferred_and_not():
         assert all(torch.equal(g, got[0]) for g in got[1:])
     finally:
         ctx.close()
+
+
+def test_a_moved_chunk_replays_the_decode_graphs():
+    """The decode launches of a call read nothing of its chunk: one token more of prefix (18 key tiles in
+    place of 17, the same items) replays the graphs of the call before."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2511_04791_amd as duet
+    from paper_2511_04791_amd import workloads as wl
+    k = 3
+    b = wl.make_batch(wl.LLAMA3_8B, [(0, 250, 1025), (1, 1, 700), (1, 1, 31)], page_seed=7103, reserve_tokens=k)
+    q, kc, vc = (t.cuda() for t in wl.make_tensors(b, 7600, device="cpu"))
+    qa, ka, va = ([t.cuda() for t in ts] for ts in wl.make_lookahead_tensors(b, k, 7601, device="cpu"))
+    pt = torch.as_tensor(b.page_table, device="cuda")
+    out, outs_a = torch.empty_like(q), [torch.empty_like(t) for t in qa]
+    ctx = duet.Context(0)
+    try:
+        ws = torch.empty(2 * duet.lookahead_workspace_bytes(wl.LLAMA3_8B, b.seq_meta, k), dtype=torch.uint8, device="cuda")
+        captured = []
+        for prefix in (1024, 1025):
+            meta = b.seq_meta.copy()
+            meta[0, 3] = prefix
+            ctx.attn_lookahead([q], qa, ka, va, [kc], [vc], pt, meta, duet.CuSplit.split(128, 128, k), outs=[out],
+                               outs_ahead=outs_a, workspace=ws, check_errors=True)
+            torch.cuda.synchronize()
+            want = ctx.attn_mixed_batch(q, kc, vc, pt, meta)
+            assert torch.equal(out, want)
+            captured.append(ctx.decode_graph_stats()["captured"])
+        assert captured[0] == captured[1] > 0
+    finally:
+        ctx.close()

@@ -18,6 +18,8 @@
 // 24 us to 5.0 us.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "kernels.h"
 #include "wave_ops.h"
 
@@ -281,10 +283,19 @@ hipError_t launch_decode_partial_f32(const AttnArgs& a, const WorkArgs& w, hipSt
 }
 
 hipError_t launch_prefill_f32(const AttnArgs& a, const WorkArgs& w, hipStream_t s) {
-  const dim3 grid(w.n_pitems * (kPrefillRows / kF32Rows));
-  if (a.head_dim == 128) hipLaunchKernelGGL(prefill_f32<128>, grid, dim3(64 * kF32Waves), 0, s, a, w);
-  else hipLaunchKernelGGL(prefill_f32<64>, grid, dim3(64 * kF32Waves), 0, s, a, w);
-  return hipGetLastError();
+  constexpr int kBlocks = kPrefillRows / kF32Rows, kThreads = 64 * kF32Waves;
+  constexpr int kItems = 1 << 19;  // of one launch: a grid holds fewer than 2^32 threads
+  static_assert((unsigned long long)kItems * kBlocks * kThreads < 1ULL << 32, "a launch fits");
+  for (int i0 = 0; i0 < w.n_pitems; i0 += kItems) {
+    WorkArgs part = w;
+    part.pitems += i0;
+    const dim3 grid(std::min(kItems, w.n_pitems - i0) * kBlocks);
+    if (a.head_dim == 128) hipLaunchKernelGGL(prefill_f32<128>, grid, dim3(kThreads), 0, s, a, part);
+    else hipLaunchKernelGGL(prefill_f32<64>, grid, dim3(kThreads), 0, s, a, part);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace duet

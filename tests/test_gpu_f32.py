@@ -88,3 +88,23 @@ def test_f32_bad_page_is_skipped_and_flagged(ctx):
     out = ctx.attn_mixed_batch(q, kc, vc, pt, b.seq_meta, check_errors=True)  # the error word is cleared
     torch.cuda.synchronize()
     assert errors(out, oracle_out(b, q, kc, vc))[0] <= F32_MAX_ABS
+
+
+def test_more_items_than_one_launch_holds(ctx):
+    """More than 2^20 one-token requests: the grid of all of them would hold 2^32 threads.  A request
+    without a prefix sees its own key only, so it returns that token's value."""
+    import paper_2511_04791_amd as duet
+    n, pages = (1 << 20) + 5, 1000
+    g = torch.Generator(device="cuda").manual_seed(7)
+    q = torch.randn(n, 1, 64, device="cuda", generator=g)
+    kc, vc = torch.randn(pages, 1, 16, 64, device="cuda", generator=g), torch.randn(pages, 1, 64, 16, device="cuda", generator=g)
+    pt = torch.randint(0, pages, (n, 1), device="cuda", generator=g, dtype=torch.int32)
+    meta = np.zeros((n, 4), np.int32)
+    meta[:, 1], meta[:, 2] = np.arange(n), 1
+    c = duet.Context(0)  # its grown staging buffer goes with it
+    try:
+        out = c.attn_mixed_batch(q, kc, vc, pt, meta, check_errors=True)
+        torch.cuda.synchronize()
+    finally:
+        c.close()
+    assert torch.equal(out[:, 0], vc[pt[:, 0].long(), 0, :, 0])

@@ -8,6 +8,8 @@
 // accesses, fp32 arithmetic, round-to-nearest-even on store.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "kernels.h"
 #include "wave_ops.h"
 
@@ -216,8 +218,14 @@ hipError_t launch_rmsnorm(const __bf16* x, const __bf16* w, __bf16* y, int rows,
 hipError_t launch_swiglu(const __bf16* gu, __bf16* a, int rows, int m, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
   const int per_row = (m / 8 + 256 * kSwigluChunks - 1) / (256 * kSwigluChunks);
-  hipLaunchKernelGGL(swiglu_bf16, dim3((unsigned)rows * per_row), dim3(256), 0, s, gu, a, m, per_row);
-  return hipGetLastError();
+  const int most = (int)(((1u << 24) - 1) / per_row);  // rows of one launch: a grid holds fewer than 2^32 threads
+  for (int r0 = 0; r0 < rows; r0 += std::min(most, rows - r0)) {
+    hipLaunchKernelGGL(swiglu_bf16, dim3(std::min(most, rows - r0) * per_row), dim3(256), 0, s, gu + (size_t)r0 * 2 * m,
+                       a + (size_t)r0 * m, m, per_row);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_qkv_split(const QkvSplitArgs& a, hipStream_t s) {

@@ -48,6 +48,20 @@ def test_swiglu_widths(ctx, m):
     assert (err <= (U + 2.0 ** -14) * np.abs(ref) + 1e-30).all()
 
 
+def test_swiglu_of_more_blocks_than_one_launch_holds(ctx):
+    """2^24 workgroups of 256 threads are one too many for a grid: the rows go in two launches."""
+    rows, m = (1 << 24) + 3, 8
+    gu = torch.randn(1 << 16, 2 * m, device="cuda").to(torch.bfloat16).repeat((rows >> 16) + 1, 1)[:rows].contiguous()
+    out = torch.full((rows, m), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ctx.swiglu(gu, out=out)
+    torch.cuda.synchronize()
+    one = ctx.swiglu(gu[:1 << 16].contiguous())
+    assert torch.equal(out[:1 << 16], one)
+    assert torch.equal(out[1 << 16:rows - 3].view(-1, 1 << 16, m), one.expand((rows >> 16) - 1, -1, -1))
+    assert torch.equal(out[rows - 3:], one[:3])
+
+
+
 CASES = {
     # whole pages, pages covered in part at either end or both, one row, every start in a page
     "pages": ((4, 2, 128), [(0, 16, 0), (0, 48, 32), (0, 17, 15), (0, 31, 1), (0, 15, 0), (0, 2, 15), (1, 1, 16)]),

@@ -1694,7 +1694,15 @@ int duet_qkv_split(duet_ctx* ctx, const duet_shape* shape, const void* qkv, void
   if (rc) return rc;
   std::lock_guard<std::mutex> lock(ctx->mu);
   Plan& p = ctx->plan;
-  plan_batch(shape, batch, 1, 1, &p, true);
+  // The workspace is laid out as for attention; the kernel reads the request table alone, so the work
+  // lists are neither made nor sent (200 decodes of 13000 to 26000 tokens: 1 MB of lists).
+  plan_batch(shape, batch, 1, 1, &p, false);
+  for (int r = 0; r < batch->num_reqs; ++r) {
+    const duet_seq_meta& m = batch->reqs[r];
+    p.meta.push_back(make_int4(m.kind, m.q_start, m.q_len, m.cached_len));
+  }
+  p.upload_bytes = align_up(p.off_meta + p.meta.size() * sizeof(int4));
+  p.n_slots = 0;
   if (workspace_bytes < p.total) return fail(DUET_EWORKSPACE, "workspace %zu bytes, need %zu", workspace_bytes, p.total);
   hipStream_t st = static_cast<hipStream_t>(stream);
   HIP_TRY(hipSetDevice(ctx->device));

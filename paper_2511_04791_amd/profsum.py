@@ -42,14 +42,22 @@ SIMDS = 1024  # 256 CUs x 4
 XCDS = 8      # rocprofv3 sums GRBM_GUI_ACTIVE over the XCDs, which share one clock
 
 
-def source_hash(name: str) -> str:
-    """Hash of a kernel's source file and of the headers with device code that it includes."""
-    with open(os.path.join(PKG, "csrc", name), "rb") as f:
-        text = f.read()
-    h = hashlib.sha256(text)
-    for header in re.findall(rb'#include "(\w+_device\.h)"', text):
-        with open(os.path.join(PKG, "csrc", header.decode()), "rb") as f:
-            h.update(f.read())
+def source_hash(name: str, folder: str = os.path.join(PKG, "csrc")) -> str:
+    """Hash of a kernel's source file and of every header of the folder that it includes, directly or
+    through another: they hold device code, and the rules of what a launch does.  Comments and
+    the space around lines are left out."""
+    h = hashlib.sha256()
+    todo, seen = [name], {name}
+    while todo:
+        with open(os.path.join(folder, todo.pop(0)), encoding="utf-8") as f:
+            text = re.sub(r"/\*.*?\*/|//[^\n]*", "", f.read(), flags=re.S)
+        for line in text.splitlines():
+            if line.strip():
+                h.update(line.strip().encode() + b"\n")
+        for header in re.findall(r'#include "([\w./]+)"', text):
+            if header not in seen and os.path.exists(os.path.join(folder, header)):
+                seen.add(header)
+                todo.append(header)
     return h.hexdigest()[:16]
 
 

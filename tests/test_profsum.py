@@ -35,3 +35,32 @@ def test_traffic_scales_by_the_copy_and_tags_the_source(tmp_path):
     assert d["fetch_bytes_per_launch"] == 1024 * 1024 * 2 and d["write_bytes_per_launch"] == 512 * 1024
     assert d["bytes_per_launch"] == 1024 * 1024 * 2 + 512 * 1024
     assert d["source_sha256_16"] == profsum.source_hash("attn_prefill.hip")
+
+
+def test_source_hash_follows_headers_and_skips_comments(tmp_path):
+    (tmp_path / "k.hip").write_text('#include <vector>\n#include "a.h"\n#include "elsewhere.h"\nint k;  // note\n')
+    (tmp_path / "a.h").write_text('#pragma once\n#include "b.h"\nint a;\n')
+    (tmp_path / "b.h").write_text('#include "a.h"\nint b = 1;\n')
+    first = profsum.source_hash("k.hip", str(tmp_path))
+    (tmp_path / "b.h").write_text('/* two\nlines */\n#include "a.h"\n\n  int b = 1;  // a remark\n')
+    assert profsum.source_hash("k.hip", str(tmp_path)) == first
+    (tmp_path / "b.h").write_text('#include "a.h"\nint b = 2;\n')
+    assert profsum.source_hash("k.hip", str(tmp_path)) != first
+
+
+def test_source_hash_of_the_kernels_covers_shared_headers():
+    import os
+    import shutil
+    import tempfile
+    csrc = os.path.join(profsum.PKG, "csrc")
+    for name in {src for _, src in profsum.KERNELS.values()}:
+        first = profsum.source_hash(name)
+        for header in ("wave_ops.h", "kernels.h"):
+            with tempfile.TemporaryDirectory() as d:
+                for f in os.listdir(csrc):
+                    if f.endswith((".h", ".hip")):
+                        shutil.copy(os.path.join(csrc, f), d)
+                assert profsum.source_hash(name, d) == first
+                with open(os.path.join(d, header), "a") as f:
+                    f.write("int changed;\n")
+                assert profsum.source_hash(name, d) != first, (name, header)

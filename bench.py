@@ -20,7 +20,7 @@ layers benchmarked (Llama-3-70B has 80 layers, Llama-3-8B 32).  Algorithm 1 runs
 calibrated, once per attention shape, on generic batches of that shape that are none of these.  Inputs are seeded, synthetic and
 resident in HBM before timing starts.
 
-Prints one JSON line.  `value` is the headline workload's wall-clock time per step over K
+Prints one JSON line of a few KB (and, before it, one with every measurement on stderr).  `value` is the headline workload's wall-clock time per step over K
 back-to-back steps between two device synchronisations (lower is better), on the split
 Algorithm 1 chose (with its k decode steps); `agg_us` is the same work on one stream.  The
 timed region runs last, on a GPU kept busy by the passes before it.  Further passes give the
@@ -432,6 +432,17 @@ def run_config(ctx, key, args, calib):
     return res
 
 
+def summary(res: dict) -> dict:
+    """A workload's entry in the printed line, which stays a few KB long; everything measured goes to
+    stderr as one JSON line before it."""
+    out = {k_: res[k_] for k_ in ("chosen", "wall_us", "agg_wall_us", "speedup_vs_agg", "iteration_us", "agg_iteration_us",
+                                  "predicted_us", "decode_step_us") if k_ in res}
+    out["decode_gbps"] = res["decode_roofline"]["split"] and res["decode_roofline"]["split"]["achieved"]
+    out["prefill_tflops"] = res["prefill_roofline"]["split"] and res["prefill_roofline"]["split"]["achieved"]
+    out["sweep_best_us"] = res["sweep_best"] and res["sweep_best"]["measured_us"]
+    return out
+
+
 def suite_main(args):
     import torch
     import paper_2511_04791_amd as duet
@@ -479,8 +490,9 @@ def suite_main(args):
                    "key": args.headline, "layers": h["layers"], "tbt_slo_us": h["tbt_slo_us"], "split": h["chosen"]},
         "agg_us": h["agg_wall_us"], "speedup_vs_agg": h["speedup_vs_agg"], "iteration_us": h["iteration_us"],
         "roofline": h["roofline"], "cpu_baseline": h["cpu_baseline"],
-        "configs": results, "calibration": calibs,
+        "configs": {k_: summary(r) for k_, r in results.items()},
     }
+    print(json.dumps({"configs": results, "calibration": calibs}), file=sys.stderr, flush=True)
     print(json.dumps(line), flush=True)
 
 

@@ -23,8 +23,9 @@ HIP_FLAGS = ["--offload-arch=" + ARCH, "-O3", "-fPIC", "-std=c++17", "-Wall",
              # atomics stay as written: the decode kernel's one-lane counter atomic must not get the
              # wave-aggregation rewrite, which reads its result right after issue
              "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
-             # loops start on 64 bytes: the same instructions at another offset made the long prefill chunk
-             # (64 query heads, 8192 tokens after 24576) 0.4% slower on 256 CUs, 0.9% on 224
+             # loops start on 64 bytes, whatever code comes before them in the file: the same instructions
+             # at another offset made the long prefill chunk (64 query heads, 8192 tokens after 24576) 0.4%
+             # slower on 256 CUs, 0.9% on 224.  This keeps its speed, it adds none.
              "-falign-loops=64",
              "-I" + INCLUDE, "-I" + CSRC]
 # MFMA accumulators in VGPRs: the online-softmax rescale works on them in place.

@@ -6,7 +6,9 @@
 // the prefill items, longest first, and the last ones more decode waves, which join the item queues as
 // CUs run out of prefill work: whichever half lasts longer ends on every CU.
 //
-// A workgroup of either kind fills a CU (the prefill ring takes its LDS).  While prefill items last,
+// With heads of 128 a workgroup of either kind fills a CU (the prefill ring takes its LDS).  With heads of
+// 64 the ring is 64 of 160 KiB and registers are the limit: eight waves of 156 leave no room for eight
+// more, but a decode workgroup, four of whose waves end at once, does.  While prefill items last,
 // decode runs on decode_blocks CUs: the number at which four waves each keep the memory busy (a wave
 // streams about 10 GB/s; eight waves per CU halve that and leave each twice as long with its
 // last item).  One layer of 64 decodes (452 MB) beside 2048 new tokens, Llama-3-8B: decode 92 us and
@@ -14,8 +16,7 @@
 // four waves, and 134 us with 160 blocks of eight.  Heads of 64 read half as much per page and want
 // more (100 decodes beside 2048 tokens: 65 / 64 / 57 us with 128 / 160 / 192 blocks).
 //
-// A batch of few decode items (decode_small) runs them first, one workgroup each.
-//
+// A batch of few or short decode items (decode_small) runs them first, as launched alone.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

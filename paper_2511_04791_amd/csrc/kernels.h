@@ -265,12 +265,15 @@ hipError_t launch_prefill(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
 // Merges the units that ran as pieces (bf16; launch_prefill and launch_mixed end with it).
 hipError_t launch_prefill_merge(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
 // Both bf16 halves of a layer in one launch, where that gains: not when prefill lasts so much longer
-// that decode hardly matters (921,000 key tiles beside 1024 decode items: 0.6% slower in one launch;
-// 65,000 beside 1,100: 5% faster), nor for many small decode items, two of which fit on a CU that
+// that decode hardly matters, nor for many small decode items, two of which fit on a CU that
 // runs no prefill (us a layer, one launch against two: 512 new tokens beside 32 items 25 / 34,
-// beside 1600 items 84 / 79; 64 tokens beside 800 items 33 / 32).  Heads of 64 keep the rule, though their
-// prefill alone may run two workgroups per CU (16 / 2 heads, 100 decodes: beside 8192 tokens 193 / 228,
-// beside 8192 after 8192 543 / 515).
+// beside 1600 items 84 / 79; 64 tokens beside 800 items 33 / 32).  One launch against two, heads of 128, by
+// key tiles per decode item: 59, 5% faster; 100 to 256, from 7% faster (8 / 1 heads, 4096 tokens after
+// 16384 beside 64 decodes 372 / 399) to 1.4% slower (64 / 8 heads, 8192 after 8192 beside 64, 3043 / 3000),
+// 1.4% faster on average; past 256, within 2.6% either way, but 8 / 1 heads still 1 to 7% faster.
+// Heads of 64 keep the rule: one launch is 5 to 20% faster but where a long chunk's prefill alone runs
+// two workgroups per CU (16 / 2 heads, 100 decodes: beside 8192 tokens 220 / 264, after 8192 557 / 542, after
+// 24576 1191 / 1106).
 constexpr int kMixedMaxTilesPerItem = 256;
 constexpr int kMixedMaxSmallItems = 512;
 inline bool use_mixed(const WorkArgs& w) {

@@ -331,7 +331,7 @@ int duet_attn_mixed_batch(duet_ctx* ctx, const duet_shape* shape, const void* q,
  * workspace is a file-scope device array of DUET_NOALLOC_SCRATCH_BYTES held by each device the
  * library runs on until the process ends; the call allocates nothing (no device or pinned memory,
  * no streams, no events).  Batches whose work lists and partials need more return
- * DUET_EWORKSPACE, as do work lists beyond the 2 MiB of pinned staging duet_init preallocates.
+ * DUET_EWORKSPACE, as do work lists beyond the pinned staging duet_init preallocates (2 MiB and 16 KiB).
  * Under DUET_SPLIT or DUET_CONCURRENT the CU-masked streams must already exist: one earlier call
  * of duet_attn_mixed_batch or duet_attn_iteration with the same split creates them (the context
  * keeps the streams of its most recently used split or mode); otherwise DUET_EINVAL.  Profiling

@@ -190,6 +190,9 @@ constexpr int kPrefillTailMinTiles = 16;
 // tokens) 513 / 529; five (8 / 1 heads, 1500 tokens after 900) 35.7 / 40.1; eight (4 / 4 heads, 2048
 // after 2048) 42.4 / 33.2; 16 (32 / 8 heads, 16 tokens after 8000) 51.7 / 30.0; 33 (4 / 4 heads, 512
 // after 16384) 88.6 / 44.5.
+// Units of more than six beside units of fewer (us a layer, 1500 tokens after 2341, 8 / 1 heads, on 256 CUs;
+// 872 after 2341, 8 / 2 heads, on 160): each by its last piece 42 / 50; the short ones so and the long ones
+// by the kernel 48 / 57; all by the kernel 37 / 44.
 constexpr int kPrefillSelfMerge = 6;
 static_assert(kPrefillTailPieces <= kPrefillSelfMerge, "the tail split merges itself");
 static_assert(2 * kPrefillPieceFill + kPrefillPieceFill * kPrefillTailPieces <= 0xffff, "a slot fits 16 bits");

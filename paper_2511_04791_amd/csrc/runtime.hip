@@ -55,7 +55,7 @@ constexpr size_t kMaxGraphs = 128;    // cached decode-step graphs per context
 // (duet_init, with the device current) and is kept in the context.
 constexpr size_t kScratchBytes = size_t(66) << 20;
 // Pinned staging allocated up front for each slot, so that the no-allocation path never grows it.
-constexpr size_t kStagingPrealloc = size_t(2) << 20;
+constexpr size_t kStagingPrealloc = (size_t(2) << 20) + (size_t(16) << 10);
 
 inline size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 
@@ -221,7 +221,12 @@ void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps,
   const int P = bf16 && total_tiles > 0 ? prefill_piece_tiles_for(total_tiles) : 0;
   p->prefill_tiles = bf16 ? total_tiles : 0;
   // Units longer than 1.5 P: n pieces of equal length (the last may be shorter), none empty.
-  auto pieces_of = [&](int nt) { return P > 0 && 2 * nt > 3 * P ? (nt + P - 1) / P : 1; };
+  auto equal = [](int nt, int n) {
+    const int len = (nt + n - 1) / n;
+    return (nt + len - 1) / len;
+  };
+  auto pieces_of = [&](int nt) { return P > 0 && 2 * nt > 3 * P ? equal(nt, (nt + P - 1) / P) : 1; };
+  int most_pieces = 1;
   // Tail split: when the whole units (those the rule above leaves in one piece) number more than
   // two rounds of one workgroup per CU of the whole chip, the shortest round of them -- the last
   // dispatched -- runs as kPrefillTailPieces pieces each (of at least kPrefillTailMinTiles
@@ -238,6 +243,7 @@ void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps,
       if (q.kind != DUET_KIND_PREFILL) continue;
       for (int t = 0; t * rows < q.q_len; ++t) {
         const int nt = block_tiles(q, t);
+        most_pieces = std::max(most_pieces, pieces_of(nt));
         if (pieces_of(nt) == 1) {
           whole.push_back({nt, r, t});
           n_whole_units += units;
@@ -271,16 +277,16 @@ void plan_batch(const duet_shape* s, const duet_batch* b, int layers, int steps,
     for (int t = 0; t * rows < q.q_len; ++t) {
       const int nt = block_tiles(q, t);
       int pieces = pieces_of(nt);
+      // One unit of many pieces brings the merge kernel; it then takes every unit of the key split.
+      const bool kernel_merges = pieces > 1 && most_pieces > kPrefillSelfMerge;
       if (pieces == 1 && std::binary_search(tail_blocks.begin(), tail_blocks.end(), std::make_pair(r, t)))
-        pieces = kPrefillTailPieces;
+        pieces = equal(nt, kPrefillTailPieces);
       const int len = (nt + pieces - 1) / pieces;
-      pieces = (nt + len - 1) / len;
       n_pitems += (int64_t)pieces * units;
       // Unit u's query heads from head(u) on.  Units are ordered so that workgroup index mod 8 follows the
       // kv head: the units sharing one kv head land on one XCD and share its L2.
       auto head = [&](int u) { return nh == 1 ? (u % s->num_kv_heads) * g + u / s->num_kv_heads : u * nh; };
       const int slot0 = n_slots;
-      const bool kernel_merges = pieces > kPrefillSelfMerge;
       if (kernel_merges) {
         if (fill)
           for (int u = 0; u < units; ++u)

@@ -275,12 +275,20 @@ hipError_t launch(const SkinnyArgs& a, hipStream_t s) {
 
 }  // namespace
 
-bool use_skinny(int rows, int cus, size_t weight_bytes, int widest, size_t bytes) {
+bool use_skinny(int rows, int cus, int d, int d_qkv, int m, size_t bytes) {
+  const int widest = std::max(d, d_qkv);
   if (rows < 1 || rows > kSkinnyRows || (size_t)rows * widest * sizeof(float) > bytes) return false;
-  if (cus == DUET_TOTAL_CUS) return true;
-  if (rows <= kSkinnyRows / 2 && cus >= 96) return weight_bytes <= (size_t)512 << 20;
-  const size_t tile_rows = rows <= 16 ? 16 : rows <= 32 ? 32 : 64;
-  return weight_bytes <= (size_t)64 << 20 && tile_rows * weight_bytes <= (size_t)18000000 * std::min(cus, 128);
+  const bool whole = cus == DUET_TOTAL_CUS;
+  const size_t weights = (size_t)d * (d_qkv + d + 3 * (size_t)m) * sizeof(__bf16);
+  // Rows (of whole tiles) times weights that a share of `cus` CUs takes.
+  const size_t most = (size_t)18000000 * std::min(cus, 128);
+  if (rows > kSkinnyRows / 2) {
+    const bool narrow = widest <= 1536;
+    return whole ? narrow || m >= 2 * d : narrow && kSkinnyRows * weights <= most;
+  }
+  if (whole) return true;
+  if (cus >= 96) return weights <= (size_t)512 << 20;
+  return weights <= (size_t)64 << 20 && (rows <= 16 ? 16 : 32) * weights <= most;
 }
 
 // Parts of d_in: about one workgroup per CU of the whole chip, each wave with a step of its own, partials

@@ -217,30 +217,25 @@ struct QkvSplitArgs {
 };
 
 // Projections of few rows (gemm_skinny.hip) instead of the library's, for a partition of `rows` rows on
-// `cus` CUs whose layer holds `weight_bytes` of projection weights: where one part of its widest product,
-// [rows, widest] in fp32, fits in `bytes` (more than 131072 columns at 64 rows do not).  On the whole
-// chip the own kernels win for every size measured up to 64 rows (above).  On a share they pull weights
-// at about 30 GB/s a CU, somewhat below the library's kernels, and past 32 rows their products grow with
-// the rows (16, 32 or 64), so they lose where rows times weights are large for the CUs.  Us per layer
-// of four, own against the library's, on 128 / 96 / 64 / 32 CUs (the library's calls cost the host about
-// 84 us a layer, which is what the smallest sizes show):
-//   436 MB (Llama-3-8B), 16 rows: 192 / 241 / 294 / 492 against 208 / 251 / 267 / 435;
-//                        32 rows: 212 / 285 / 357 / 613 against 256 / 312 / 399 / 648;
-//                        64 rows: 260 / 355 / 454 / 797 against 284 / 319 / 377 / 585;
-//   126 MB, 16 rows: 83 / 108 against 119 / 147 on 128 and 96 CUs;
-//   50 MB, 16 rows: 74 / 77 / 83 / 116 against 86 / 85 / 85 / 92;
-//          32 rows: 83 / 89 / 99 / 152 against 86 / 87 / 88 / 121;
-//          64 rows: 100 / 112 / 128 / 211 against 91 / 105 / 110 / 140;
-//   30 MB, 16 rows: 61 / 63 / 63 / 81 against 84 / 85 / 84 / 85;
-//          32 rows: 68 / 72 / 72 / 99 against 85 / 85 / 85 / 86;
-//          64 rows: 81 / 87 / 87 / 128 against 86 / 87 / 86 / 92;
-//   17 MB, 32 rows: 66 / 66 / 66 / 75 against 84 / 85 / 85 / 85;
-//          64 rows: 79 / 79 / 79 / 96 against 85 / 85 / 84 / 85;
-//   11 MB, 64 rows: 77 / 79 / 79 / 90 against 85 / 84 / 84 / 85.
+// `cus` CUs and layers of model width d, QKV width d_qkv and MLP width m: where one part of the widest product in
+// fp32 fits in `bytes` (at 64 rows more than 131072 columns do not), and where they are faster.  A layer
+// behind 130 us of attention (us gained over the library's kernels and the operators they fuse), whole chip / 128 /
+// 96 / 64 / 32 CUs:
+//   up to 32 rows they gain on the whole chip for every size (436 MB of weights, Llama-3-8B, 16 rows 78; 6 MB 2), and
+//   from 96 CUs on up to 436 MB (16 rows: 436 MB 78 / 24 / 11; 50 MB 16 / 14 / 17); below that the weights a CU
+//   pulls count, at about 30 GB/s (16 rows: 30 MB 15 / 17 / 17 / 17 / 17, 436 MB on 64 and 32 CUs -30 and -60; 32 rows:
+//   30 MB on 32 CUs 9, 201 MB 23), and the host's share: a library call costs it about 20 us, which the own
+//   kernels' fewer launches save where nothing else is slower, so sizes with little to gain keep to
+//   rows times weights against the CUs;
+//   past 32 rows the partial sums of products of d columns weigh as much as the weights: behind narrow MLPs, whose
+//   gate-up has few workgroups too, they lose (64 rows, d 1536: m 512 -5 / -6 / . / -17, m 1584 2 / 1 / . / -20,
+//   m 4096 10 / 3 / 4 / -7 / -57; d 2048: m 512 -3 / -12 / . / -32, m 4096 9 / -5 / -14 / -29 / -108); widths near 1024
+//   gain on every share their weights suit (17 MB 9 / 10 / 9 / 10 / -2), and MLPs of twice d and more on the
+//   whole chip (436 MB 78, d 2048 with m 6144 27).
 // The two round their sums in different orders, so a block's result may differ in its last bits between
 // shares on different sides of the rule.
 constexpr int kSkinnyRows = 64;
-bool use_skinny(int rows, int cus, size_t weight_bytes, int widest, size_t bytes);
+bool use_skinny(int rows, int cus, int d, int d_qkv, int m, size_t bytes);
 struct SkinnyArgs {
   const __bf16* x;  // [rows, d_in]
   const __bf16* w;  // [d_in, d_out]

@@ -1379,7 +1379,6 @@ int block_forward(duet_ctx* ctx, const duet_shape* shape, const duet_block_shape
   __bf16* actb = reinterpret_cast<__bf16*>(ws + B.act);
   const char* msg = nullptr;
   // The own projection kernels read weights 16 bytes at a time.
-  const size_t weight_bytes = (size_t)d * (d_qkv + d + 3 * (size_t)m) * 2;
   bool weights_aligned = true;
   for (int l = 0; l < layers; ++l)
     for (const void* p : {wts[l].w_qkv, wts[l].w_o, wts[l].w_gate_up, wts[l].w_down})
@@ -1405,7 +1404,7 @@ int block_forward(duet_ctx* ctx, const duet_shape* shape, const duet_block_shape
     al.out = step_dreq ? ab + r0 * d : ab;
     // Few rows: own projection kernels, whose finishing kernels run the operator that follows; the
     // norm before a layer comes with the layer before it.
-    const bool skinny = weights_aligned && use_skinny(pt.rows, pt.cus, weight_bytes, std::max(d_qkv, d), kGemmWorkspaceBytes);
+    const bool skinny = weights_aligned && use_skinny(pt.rows, pt.cus, d, d_qkv, m, kGemmWorkspaceBytes);
     float* part = static_cast<float*>(pt.gemm_ws);
     auto project = [&](const __bf16* in, const void* wm, int d_in, int d_out, int* splits) {
       *splits = skinny_splits(pt.rows, d_in, d_out, kGemmWorkspaceBytes);

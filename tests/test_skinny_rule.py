@@ -10,8 +10,8 @@ BUFFER = 32 * MIB  # the partials' buffer of a partition
 
 @pytest.fixture(scope="module")
 def rule(native):
-    use = native["_ZN4duet10use_skinnyEiimim"]  # use_skinny(rows, cus, weight_bytes, widest, bytes)
-    use.argtypes, use.restype = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_int, ctypes.c_size_t], ctypes.c_bool
+    use = native["_ZN4duet10use_skinnyEiiiiim"]  # use_skinny(rows, cus, d, d_qkv, m, bytes)
+    use.argtypes, use.restype = [ctypes.c_int] * 5 + [ctypes.c_size_t], ctypes.c_bool
     return use
 
 
@@ -29,7 +29,7 @@ def test_partials_fit_their_buffer(rule, splits):
         for group in (1, 8, 16):
             d, d_qkv = kv * group * 128, kv * (group + 2) * 128
             for rows in (1, 16, 57, 58, 63, 64):
-                if not rule(rows, 256, 1 << 40, max(d, d_qkv), BUFFER):
+                if not rule(rows, 256, d, d_qkv, 2 * d, BUFFER):
                     refused += 1
                     continue
                 for d_in, d_out in ((d, d_qkv), (d, d), (28672, d)):
@@ -37,12 +37,19 @@ def test_partials_fit_their_buffer(rule, splits):
     assert refused  # 64 rows of 57 kv heads need 33.6 MB
 
 
-@pytest.mark.parametrize("rows,mb,cus,own", [
-    (1, 12, 8, False), (16, 29, 32, True), (16, 50, 32, False), (32, 17, 32, True), (32, 30, 32, False),
-    (33, 11, 32, False), (64, 9, 32, True), (16, 50, 64, True), (16, 75, 64, False), (32, 30, 64, True),
-    (32, 50, 64, False), (64, 17, 64, True), (64, 30, 64, False), (64, 17, 96, True), (64, 50, 128, False),
-    (64, 30, 128, True), (64, 50, 224, False), (32, 500, 96, True), (33, 500, 96, False), (32, 500, 88, False),
-    (32, 600, 224, False), (64, 1700, 256, True), (65, 1, 256, False), (0, 1, 256, False)])
-def test_both_sides_of_the_rule(rule, rows, mb, cus, own):
-    """On a share the own kernels run only where they were measured no slower than the library's."""
-    assert rule(rows, cus, mb * 1000000, 1024, BUFFER) == own
+WIDTHS = {  # d, d_qkv, m: 6, 17, 30, 17, 50, 75, 436 MB and 1.7 GB of weights a layer
+    "6": (1024, 1280, 256), "17": (1024, 1280, 2048), "30": (1024, 1280, 4096), "17w": (1536, 2560, 512),
+    "50": (1536, 2560, 4096), "75": (2048, 4096, 4096), "436": (4096, 6144, 14336), "1711": (8192, 10240, 28672)}
+
+
+@pytest.mark.parametrize("rows,widths,cus,own", [
+    (16, "30", 32, True), (16, "50", 32, False), (32, "17", 32, True), (32, "30", 32, False), (16, "17", 8, False),
+    (16, "50", 64, True), (16, "75", 64, False), (32, "30", 64, True), (32, "50", 64, False), (17, "50", 64, False),
+    (32, "436", 96, True), (32, "436", 88, False), (32, "1711", 224, False), (32, "1711", 256, True),
+    (64, "6", 32, True), (64, "17", 32, False), (64, "17", 64, True), (64, "30", 64, False), (64, "30", 128, True),
+    (33, "17w", 128, False), (33, "50", 224, False), (33, "17w", 256, False), (32, "17w", 256, True),
+    (64, "50", 256, True), (64, "75", 256, True), (64, "436", 256, True), (64, "436", 224, False), (64, "17", 256, True),
+    (65, "17", 256, False), (0, "17", 256, False)])
+def test_both_sides_of_the_rule(rule, rows, widths, cus, own):
+    """The own kernels run only where they were measured no slower than the library's."""
+    assert rule(rows, cus, *WIDTHS[widths], BUFFER) == own

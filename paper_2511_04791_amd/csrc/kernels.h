@@ -271,12 +271,16 @@ hipError_t launch_prefill_merge(const AttnArgs& a, const WorkArgs& w, hipStream_
 // 1.4% faster on average; past 256, within 2.6% either way, but 8 / 1 heads still 1 to 7% faster.
 // Heads of 64 keep the rule: one launch is 5 to 20% faster but where a long chunk's prefill alone runs
 // two workgroups per CU (16 / 2 heads, 100 decodes: beside 8192 tokens 220 / 264, after 8192 557 / 542, after
-// 24576 1191 / 1106).
+// 24576 1191 / 1106), and where hardly any prefill is beside decode that lasts about three items a wave, whose
+// waves sit on fewer CUs (2686 items beside 10 tokens 86 / 76, beside 512 96 / 100; 3406 beside 10 to 200
+// tokens 111 to 116 / 95 to 100; but 1268 items beside 64 53 / 58, 7108 beside 200 0.98 of two): there two launches.
 constexpr int kMixedMaxTilesPerItem = 256;
 constexpr int kMixedMaxSmallItems = 512;
-inline bool use_mixed(const WorkArgs& w) {
-  return w.n_ditems > 0 && w.n_pitems > 0 && w.prefill_tiles <= (long long)kMixedMaxTilesPerItem * w.n_ditems &&
-         !(w.decode_small && w.n_ditems > kMixedMaxSmallItems);
+inline bool use_mixed(const AttnArgs& a, const WorkArgs& w) {
+  if (w.n_ditems == 0 || w.n_pitems == 0 || (w.decode_small && w.n_ditems > kMixedMaxSmallItems)) return false;
+  if (a.head_dim == 64 && !w.decode_small && w.n_ditems > 2048 && w.n_ditems <= 6144 && 16 * w.prefill_tiles < w.n_ditems)
+    return false;
+  return w.prefill_tiles <= (long long)kMixedMaxTilesPerItem * w.n_ditems;
 }
 hipError_t launch_mixed(const AttnArgs& a, const WorkArgs& w, hipStream_t s);
 // The fp32 paths of the two launchers above.

@@ -824,7 +824,7 @@ int attn_layers(duet_ctx* ctx, const duet_shape* shape, int layers, const void* 
   const bool defer = has_decode && shape->dtype == DUET_BF16 && !w.decode_small;
   // Aggregated, a layer's two halves are one launch (attn_mixed.hip); per-kernel profiling keeps them
   // apart.
-  const bool mixed = !forked && !prof && shape->dtype == DUET_BF16 && use_mixed(w);
+  const bool mixed = !forked && !prof && shape->dtype == DUET_BF16 && use_mixed(a, w);
   for (int l = 0; l < layers; ++l) {
     const AttnArgs al = layer_args(l);
     if (has_decode) {
@@ -1434,7 +1434,7 @@ int block_forward(duet_ctx* ctx, const duet_shape* shape, const duet_block_shape
     qs.rows = pt.rows;
     if (skinny) HIP_TRY(launch_qkv_finish(part, splits, qkv, qs, pt.st));
     else HIP_TRY(launch_qkv_split(qs, pt.st));
-    const bool mixed = pt.decode && pt.prefill && use_mixed(wl);
+    const bool mixed = pt.decode && pt.prefill && use_mixed(al, wl);
     if (mixed) HIP_TRY(launch_mixed(al, wl, pt.st));
     else if (pt.decode) HIP_TRY(launch_decode_partial(al, wl, pt.st));
     if (pt.decode) HIP_TRY(launch_decode_reduce(al, wl, pt.st));

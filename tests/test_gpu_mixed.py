@@ -81,3 +81,18 @@ def test_bad_pages_of_either_half_are_flagged(ctx, reqs):
     out = ctx.attn_mixed_batch(q, kc, vc, pt, b.seq_meta, check_errors=True)
     torch.cuda.synchronize()
     assert not torch.isnan(out).any()
+
+
+@pytest.mark.parametrize("chunk", [10, 1200])
+def test_heads_of_64_beside_a_short_and_a_long_chunk(ctx, chunk):
+    """2600 decode items of heads of 64: two launches beside ten tokens, one beside 1200.  Same bits as split."""
+    import paper_2511_04791_amd as duet
+    from paper_2511_04791_amd import workloads as wl
+    b = wl.make_batch(wl.AttnShape(16, 2, 64, "bf16"), [(1, 1, 2000 + 17 * i % 1000) for i in range(260)] + [(0, chunk, 80)],
+                      page_seed=880)
+    q, kc, vc = wl.make_tensors(b, 8800, device="cuda")
+    pt = torch.as_tensor(b.page_table, device="cuda")
+    out = ctx.attn_mixed_batch(q, kc, vc, pt, b.seq_meta, check_errors=True)
+    other = ctx.attn_mixed_batch(q, kc, vc, pt, b.seq_meta, duet.CuSplit.split(128, 128), check_errors=True)
+    torch.cuda.synchronize()
+    assert torch.isfinite(out).all() and torch.equal(out, other)
